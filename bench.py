@@ -60,7 +60,7 @@ B_STUDY = 4096
 NAMED = ("gemm_design_sweep", "gemm_1024_a100", "flash_attention_b8_h32_s4096", "splitkv_decode_b64",
          "decoder_layer_prefill_2048")
 STUDIES = ("pipelining", "noc", "l2lru", "txn")
-KERNEL_SOURCES = ("gts_window.hip", "gts_sim.hip", "gts_common.h", "gts_dev.h")
+KERNEL_SOURCES = ("gts_team.hip", "gts_window.hip", "gts_sim.hip", "gts_common.h", "gts_wave.h", "gts_dev.h")
 PROFILES = os.path.join(ROOT, "profiles")
 
 

@@ -27,6 +27,7 @@ KERNELS = (("gts_sim.hip", (), "gts_sim.o"),
            ("gts_window.hip", ("-DGTS_WINDOW_PART=0",), "gts_window0.o"),
            ("gts_window.hip", ("-DGTS_WINDOW_PART=1",), "gts_window1.o"),
            ("gts_window.hip", ("-DGTS_WINDOW_PART=2",), "gts_window2.o"),
+           ("gts_team.hip", (), "gts_team.o"),
            ("gts_noalloc.hip", (), "gts_noalloc.o"))
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"]
 

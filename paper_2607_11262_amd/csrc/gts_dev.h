@@ -199,6 +199,8 @@ struct Launch {
   uint32_t qp;                 // windowed kernel: later ready entries per lane held in LDS
   uint32_t noc_words;          // general kernel: NoC server words after the per-SM servers
   uint32_t clocks;             // windowed kernel: time its phases with the shader clock
+  uint32_t team_ring;          // team kernel: memory arrivals per SM held in LDS
+  uint32_t team_ret;           // team kernel: pending retirements held in LDS
   uint32_t srv_one;            // one server word per compute class (every compute op holds every subpartition
                                // lane of every record, so their lanes' times stay equal)
 };
@@ -265,6 +267,54 @@ __host__ __device__ inline WinLds win_lds(uint32_t P, uint32_t NS, uint32_t SS, 
   L.t_next = take(txn ? kWinCap : 0u, false);
   L.t_max = take(txn ? kWinCap : 0u, false);
   L.t_start = take(txn ? kWinCap : 0u, false);
+  L.total = o;
+  return L;
+}
+
+// Team kernel: the same limits but for its own batch, one SM per thread.  LDS
+// carve-up as above: the parts of fixed size, then the parts sized by the
+// launch, arrays per SM strided by the workgroup's TH threads.
+constexpr uint32_t kTeamCap = 256;    // memory arrivals (or retirements) per window
+constexpr uint32_t kTeamHeads = 6;    // of one SM's arrivals (the window is cut where more may be due)
+constexpr uint32_t kTeamKey = 0;      // batch keys, and eight past the end
+constexpr uint32_t kTeamOp = kTeamKey + 2u * (kTeamCap + 8u);
+constexpr uint32_t kTeamMend = kTeamOp + kTeamCap;
+constexpr uint32_t kTeamSorted = kTeamMend + kTeamCap;           // four words per arrival
+constexpr uint32_t kTeamExch = kTeamSorted + 4u * kTeamCap;      // two halves of four words per wave
+// dispatch state: next CTA, retired CTAs, current kernel, its first and end
+// CTA, the kernel whose start cycle is known, that cycle (words 0-6), CTA
+// slots per SM (u64, words 8-9), the running kernel, the window end after
+// the retirement phase, whether some thread gave up (words 10-12)
+constexpr uint32_t kTeamCtl = kTeamExch + 32u;
+constexpr uint32_t kTeamNextCta = kTeamCtl;
+constexpr uint32_t kTeamRed = kTeamCtl + 16u;      // two windows' words {earliest ready or arrival, retirement}
+constexpr uint32_t kTeamRetCnt = kTeamRed + 4u, kTeamRetMin = kTeamRetCnt + 1u;
+constexpr uint32_t kTeamFixedInit = kTeamRetMin + 1u - kTeamCtl;
+constexpr uint32_t kTeamFixed = (kTeamRetMin + 1u + 3u) & ~3u;
+static_assert(kTeamSorted % 4 == 0 && kTeamExch % 4 == 0 && kTeamCtl % 2 == 0 && kTeamFixedInit <= 64, "alignment");
+struct TeamLds {
+  uint32_t optab, q, ret, srv, q_cnt, q_min, res, ring;
+  uint32_t total;
+};
+// TH: threads; P: op table entries (ops, then template class x slot entries);
+// SS: server words per SM; QP, RL, RT: ready entries and memory arrivals per
+// SM, and pending retirements held in LDS.
+__host__ __device__ inline TeamLds team_lds(uint32_t TH, uint32_t P, uint32_t SS, uint32_t QP, uint32_t RL, uint32_t RT) {
+  TeamLds L;
+  uint32_t o = kTeamFixed;
+  auto take = [&o](uint32_t words) {
+    const uint32_t r = o;
+    o += words;
+    return r;
+  };
+  L.optab = take(4u * P);
+  L.q = take(2u * QP * TH);
+  L.ret = take(2u * RT);
+  L.srv = take(SS * TH);
+  L.q_cnt = take(TH);
+  L.q_min = take(TH);
+  L.res = take(TH);
+  L.ring = take(3u * RL * TH);
   L.total = o;
   return L;
 }

@@ -21,6 +21,7 @@
 namespace gts {
 hipError_t launch_sim(const Launch& L, uint32_t lds_bytes, hipStream_t stream);
 hipError_t launch_window(const Launch& L, uint32_t lds_bytes, hipStream_t stream);
+hipError_t launch_team(const Launch& L, uint32_t lds_bytes, hipStream_t stream);
 }
 
 struct gts_graph {
@@ -670,6 +671,44 @@ uint32_t device_cus() {
   return c;
 }
 
+// The team kernel (one workgroup per simulation, a wave per 64 SMs) takes the
+// batch: it shortens a simulation's chain at the price of more work, which
+// pays while wave slots are idle.  Measured, windowed / team: split-KV decode
+// (130,576 nodes) x 1024 records 93.3 / 49.9 ms, flash attention (659,456) x
+// 256 198 / 113 ms; at 4096 records a 24,832-node GEMM 11.1 / 10.6 ms and a
+// 401,408-node one 229 / 268 ms.
+bool team_batch(uint32_t mode, uint32_t B) {
+  constexpr uint32_t kTeamMost = 1024;
+  return mode == gts::kWinPlain && B <= kTeamMost;
+}
+
+// LDS one workgroup may have on the current device (0 if it cannot be queried).
+uint32_t device_lds() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || n <= 0)
+    return 0;
+  return (uint32_t)n;
+}
+
+// LDS bytes of a team launch, its list sizes chosen for the workgroups a CU
+// will hold.
+uint32_t team_sizes(const gts_graph* g, gts::Launch& L, uint32_t wstride) {
+  const uint32_t TH = 64u * ((L.max_nsm + 63u) / 64u), P = g->img.n_ops + g->img.n_tops;
+  const uint32_t cus = device_cus();
+  const uint32_t per_cu = cus ? std::max(1u, (L.B + cus - 1u) / cus) : 1u;
+  const uint32_t budget = 160u * 1024u / per_cu;
+  uint32_t qp = 4, rl = 6, rt = 64;
+  auto bytes = [&](uint32_t q, uint32_t r, uint32_t t) { return 4u * gts::team_lds(TH, P, wstride, q, r, t).total; };
+  struct { uint32_t q, r, t; } const up[] = {{8, 6, 64}, {8, 8, 256}, {12, 12, 256}, {16, 16, 512}, {32, 16, 512}, {64, 32, 512}};
+  for (const auto& u : up)
+    if (bytes(u.q, u.r, u.t) <= budget) qp = u.q, rl = u.r, rt = u.t;
+  L.qp = qp;
+  L.team_ring = rl;
+  L.team_ret = rt;
+  return bytes(qp, rl, rt);
+}
+
 int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_nsm, uint32_t max_nsub, uint32_t max_noc,
            uint32_t* out_cycles, uint32_t* out_makespan, int32_t* out_status, uint64_t* out_digest, uint8_t* sims,
            uint32_t flags, hipStream_t st) {
@@ -693,7 +732,7 @@ int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_
   L.max_nsm = max_nsm;
   L.max_nsub = max_nsub;
   L.noc_words = noc_words;
-  L.qp = 0;
+  L.qp = L.team_ring = L.team_ret = 0;
   const char* clocks = std::getenv("GTS_WINDOW_CLOCKS");  // diagnostics: per-phase shader clocks
   L.clocks = clocks && std::strcmp(clocks, "0") != 0 ? 1u : 0u;
 
@@ -744,15 +783,24 @@ int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_
     windowed = bytes(qp) <= kLdsBudget;
     lds_window = bytes(qp);
   }
-  // GTS_KERNEL=window (diagnostics): no general-kernel pass, so simulations
-  // the windowed kernel hands back keep their internal retry status.
+  // GTS_KERNEL=window / team (diagnostics): only that kernel, so simulations
+  // it hands back keep their internal retry status.
   const bool window_only = windowed && force && std::strcmp(force, "window") == 0;
+  const bool team_only = windowed && force && std::strcmp(force, "team") == 0;
   hipError_t e = hipSuccess;
-  if (windowed) {
+  if (windowed && !window_only && (team_only || team_batch(mode, B))) {
+    gts::Launch T = L;
+    const uint32_t lds_team = team_sizes(g, T, wstride);
+    if (lds_team <= device_lds()) {
+      e = gts::launch_team(T, lds_team, st);
+      L.retry_only = 1;
+    }
+  }
+  if (e == hipSuccess && windowed && !team_only) {
     e = gts::launch_window(L, lds_window, st);
     L.retry_only = 1;
   }
-  if (e == hipSuccess && !window_only) e = gts::launch_sim(L, lds_general, st);
+  if (e == hipSuccess && !window_only && !team_only) e = gts::launch_sim(L, lds_general, st);
   if (e != hipSuccess) return fail(GTS_E_HIP, "kernel launch: %s", hipGetErrorString(e));
   return GTS_OK;
 }

@@ -11,6 +11,7 @@
 namespace gts {
 hipError_t launch_sim(const Launch&, uint32_t, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_window(const Launch&, uint32_t, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_team(const Launch&, uint32_t, hipStream_t) { return hipErrorNoDevice; }
 }  // namespace gts
 
 extern "C" int gts_simulate_hwset_noalloc(const gts_graph*, const gts_hwset*, uint32_t, uint32_t, uint32_t*,

@@ -1,0 +1,1226 @@
+// gts_team.hip — team simulation kernel for gfx950 (MI355X): one workgroup
+// of one to four wavefronts simulates one (graph, hardware record) pair, one
+// thread per simulated SM.
+//
+// It advances a simulation through the time windows of the windowed kernel
+// (gts_window.hip states why that order equals one event at a time), but
+// spreads each window over the workgroup:
+//
+//   local phase: a thread issues its own SM's ready nodes, smallest (cycle,
+//       node id) first, straight from that SM's list; the SMs of one wave
+//       advance side by side and the waves do not wait for each other (inside
+//       a window SMs share nothing);
+//   memory phase: every thread puts its SM's due arrivals into one batch;
+//       each arrival finds its place in the batch's (cycle, id) order by
+//       counting the smaller keys, one thread per arrival; every wave then
+//       walks the ordered batch through the L2 and DRAM servers (a max-plus
+//       scan in doubles, which hold these whole numbers exactly) and
+//       completes its own SMs' arrivals, so that no wave waits for another's
+//       results;
+//   retirement and dispatch: the first wave, and only in windows that retire
+//       a CTA.
+//
+// What bounds it: a simulation is a chain of windows, and a window a chain of
+// dependent LDS and L1 / L2 accesses and of the instructions between them; a
+// batch of few simulations leaves the chip idle, so what counts is the length
+// of that chain and not the work per CU.  With one wave per simulation the
+// chain holds the packing of the taken nodes, two or three SMs per lane and a
+// 256-key sorting network; here each of them is spread over the waves or
+// gone.  The windowed kernel does less work per simulation in all, and stays
+// the faster one for large batches.
+//
+// Memory: the ready list, memory-arrival ring, servers and counts of an SM
+// lie in LDS, strided by the workgroup's threads; what does not fit goes to
+// the windowed kernel's scratch regions.  Node and CTA state is the windowed
+// kernel's.  A simulation that overflows a list is handed back.
+#include <hip/hip_runtime.h>
+
+#include "../../include/gts.h"
+#include "gts_common.h"
+#include "gts_dev.h"
+#include "gts_wave.h"
+
+namespace gts {
+
+namespace {
+
+constexpr uint32_t kBadOverflow = 1u, kBadQueue = 2u;
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+constexpr int kWaveShr1 = 0x138;
+
+extern __shared__ uint32_t team_lds_words[];
+
+// f(x) = max(x, a) + o on whole numbers below 2^53
+struct MaxPlus {
+  double a, o;
+};
+constexpr double kNegInf = -__builtin_inf();
+__device__ __forceinline__ MaxPlus after(MaxPlus f, MaxPlus g) {  // g after f
+  return MaxPlus{__builtin_fmax(f.a, g.a - f.o), f.o + g.o};
+}
+template <int ctrl, int row_mask = 0xF>
+__device__ __forceinline__ double dpp_f64(double old, double v) {
+  const uint64_t ob = __builtin_bit_cast(uint64_t, old), vb = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = dpp<ctrl, row_mask>((uint32_t)ob, (uint32_t)vb);
+  const uint32_t hi = dpp<ctrl, row_mask>((uint32_t)(ob >> 32), (uint32_t)(vb >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int ctrl, int row_mask = 0xF>
+__device__ __forceinline__ MaxPlus dpp_mp(MaxPlus c) {  // lanes without a source get the identity
+  return MaxPlus{dpp_f64<ctrl, row_mask>(kNegInf, c.a), dpp_f64<ctrl, row_mask>(0.0, c.o)};
+}
+__device__ __forceinline__ double lane_f64(double v, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, ((uint64_t)lane_u32((uint32_t)(b >> 32), l) << 32) | lane_u32((uint32_t)b, l));
+}
+__device__ __forceinline__ MaxPlus wave_incl_mp(MaxPlus c) {
+  c = after(dpp_mp<kRowShr1>(c), c);
+  c = after(dpp_mp<kRowShr2>(c), c);
+  c = after(dpp_mp<kRowShr4>(c), c);
+  c = after(dpp_mp<kRowShr8>(c), c);
+  c = after(dpp_mp<kRowBcast15, 0xA>(c), c);
+  c = after(dpp_mp<kRowBcast31, 0xC>(c), c);
+  return c;
+}
+// Wave-wide max of a u32 (uniform result).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+  x = mx(x, dpp<kRowShr1>(0u, x));
+  x = mx(x, dpp<kRowShr2>(0u, x));
+  x = mx(x, dpp<kRowShr4>(0u, x));
+  x = mx(x, dpp<kRowShr8>(0u, x));
+  x = mx(x, dpp<kRowBcast15, 0xA>(0u, x));
+  x = mx(x, dpp<kRowBcast31, 0xC>(0u, x));
+  return lane_u32(x, 63);
+}
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) { return ~wave_max_u32(~x); }
+
+// Barrier that orders LDS only: global memory is private to a thread's SM,
+// atomic, or handed over at a full barrier.
+template <uint32_t NW>
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <uint32_t NW>
+struct TSim {
+  static constexpr uint32_t TH = 64u * NW;
+  Image G;
+  const uint32_t* hw;
+  uint32_t b, x, lane, wave, nsm, nsub, smem_w, QF, RL, qcap, retl;
+  bool nocont, ofin, mem_only, sink_ret, want_digest;
+  // LDS: op table (then the template class x slot entries), servers, ready
+  // lists, rings, pending retirements
+  uint4* optab;
+  uint32_t *srv, *q_cnt, *q_min, *res, *rg_cyc, *rg_v, *rg_op;
+  uint64_t *q, *ret_l;
+  // scratch
+  uint64_t* state;
+  CtaState* cst;
+  uint32_t* mq_g;
+  gmem<uint64_t>* q_g;
+  gmem<uint64_t>* ret_g;
+  uint32_t* out_cycles;
+  // the running kernel's template (as in the windowed kernel), with the
+  // reciprocal of its nodes per CTA
+  uint32_t run_k, t_n, t_rcp, t_node0, t_kc0, t_nc, t_base, t_ops, t_nslot;
+  double l2_av, dram_av;
+  // this SM's ring: first entry and count in LDS, then in scratch
+  uint32_t rh, rc, gh, gc;
+  uint32_t red_next;  // LDS word: earliest cycle pushed for the next window
+  uint64_t digest;
+  uint32_t makespan, nfin, bad, n_issued;
+
+  __device__ __forceinline__ static uint32_t* lds() { return team_lds_words; }
+  // SM s runs on thread (s mod NW) * 64 + s / NW: consecutive SMs on
+  // different waves, so the waves carry the same number of them
+  __device__ __forceinline__ static uint32_t sm_of(uint32_t t) { return (t & 63u) * NW + (t >> 6); }
+  __device__ __forceinline__ static uint32_t thread_of(uint32_t s) { return (s % NW) * 64u + s / NW; }
+
+  // ---- ready list of thread t's SM: entries (cycle << 32 | node), [0, QF)
+  // in LDS and the rest in scratch, in no order; q_min a lower bound of the
+  // cycles outside the local phase
+  __device__ __forceinline__ uint64_t q_get(uint32_t t, uint32_t i) const {
+    return i < QF ? q[i * TH + t] : q_g[(i - QF) * TH + t];
+  }
+  __device__ __forceinline__ void q_set(uint32_t t, uint32_t i, uint64_t k) {
+    if (i < QF)
+      q[i * TH + t] = k;
+    else
+      q_g[(i - QF) * TH + t] = k;
+  }
+  // outside the local phase any thread may push to any SM's list
+  __device__ __forceinline__ void push(uint32_t t, uint32_t cyc, uint32_t v) {
+    const uint32_t i = atomicAdd(&q_cnt[t], 1u);
+    if (i < qcap) {
+      q_set(t, i, ((uint64_t)cyc << 32) | v);
+      atomicMin(&q_min[t], cyc);
+    } else {
+      bad |= kBadQueue;
+    }
+  }
+
+  // ---- pending retirements (cycle << 32 | thread), the first retl in LDS
+  __device__ __forceinline__ uint64_t ret_get(uint32_t i) const { return i < retl ? ret_l[i] : ret_g[i - retl]; }
+  __device__ __forceinline__ void ret_set(uint32_t i, uint64_t k) {
+    if (i < retl)
+      ret_l[i] = k;
+    else
+      ret_g[i - retl] = k;
+  }
+  __device__ __forceinline__ void ret_push(uint32_t cyc) {
+    const uint32_t i = atomicAdd(lds() + kTeamRetCnt, 1u);
+    if (i < kRetireCap) {
+      ret_set(i, ((uint64_t)cyc << 32) | x);
+      if (i >= retl) mem_wait();  // the first wave reads it after a barrier that orders LDS only
+      atomicMin(lds() + red_next + 1u, cyc);
+    } else {
+      bad |= kBadQueue;
+    }
+  }
+
+  __device__ __forceinline__ void record(uint32_t v, uint32_t s, uint32_t f) {
+    const uint64_t w = ((uint64_t)f << 32) | s;
+    if (out_cycles) reinterpret_cast<uint64_t*>(out_cycles)[(uint64_t)b * G.n_nodes + v] = w;
+    if (want_digest) digest += mix64((((uint64_t)s << 32) | f) ^ mix64((uint64_t)v + 1));
+    makespan = f > makespan ? f : makespan;
+    ++nfin;
+  }
+
+  // ---- node records: expanded, or the running kernel's template; the op
+  // field becomes an index into the LDS op table
+  __device__ __forceinline__ Rec rec_of(uint32_t v) const {
+    if (t_n == 0) return load_rec(G.nodes, v);
+    const uint32_t rel = v >= t_node0 ? v - t_node0 : 0u;  // idle lanes pass node 0
+    uint32_t ci = __umulhi(rel, t_rcp);                     // the quotient or one below it
+    uint32_t loc = rel - ci * t_n;
+    if (loc >= t_n) {
+      ++ci;
+      loc -= t_n;
+    }
+    if (ci >= t_nc || loc >= t_n) ci = loc = 0u;
+    Rec r = load_rec(G.tnodes, t_base + loc);
+    const uint32_t cq = G.cclass[t_kc0 + ci];
+    const uint32_t base = t_node0 + ci * t_n;
+    r.a.x = (r.a.x & 0xFFFF0000u) | (G.n_ops + t_ops + cq * t_nslot + (r.a.x & 0xFFFFu));
+    r.a.y = t_kc0 + ci;
+    r.a.w += base;
+    r.b.x += base;
+    r.b.y += base;
+    return r;
+  }
+  __device__ __forceinline__ void load_template(uint32_t k) {
+    const KernelDev kd = G.kernels[k];
+    run_k = k;
+    t_n = uni(kd.t_n);
+    t_rcp = t_n > 1u ? uni((uint32_t)(0x100000000ull / t_n)) : 0xFFFFFFFFu;
+    t_node0 = uni(kd.node_begin);
+    t_kc0 = uni(kd.cta_begin);
+    t_nc = uni(kd.cta_end) - t_kc0;
+    t_base = uni(kd.t_base);
+    t_ops = uni(kd.t_ops & 0xFFFFu);
+    t_nslot = uni(kd.t_ops >> 16);
+    sink_ret = uni(kd.pad[0]) != 0;
+  }
+
+  // ---- local phase: this SM's list is [due | later]: n entries, the first
+  // nd of them due, mn the earliest of the rest
+  uint32_t n, nd, mn;
+  __device__ __forceinline__ void push_own(uint32_t cyc, uint32_t v, uint32_t H) {
+    if (n >= qcap) {
+      bad |= kBadQueue;
+      return;
+    }
+    const uint64_t k = ((uint64_t)cyc << 32) | v;
+    if (cyc < H) {
+      if (nd != n) q_set(x, n, q_get(x, nd));
+      q_set(x, nd, k);
+      ++nd;
+    } else {
+      q_set(x, n, k);
+      mn = cyc < mn ? cyc : mn;
+    }
+    ++n;
+  }
+
+  // Release along one edge into a shared node (atomics; the target may be in
+  // another CTA on another SM).  H: the window end in the local phase (the
+  // target is then on this SM), 0 in the memory phase.
+  __device__ __forceinline__ void release_shared(uint32_t w, uint32_t r, uint32_t src_cta, uint32_t H) {
+    atomicMax(st_acc(&state[w]), r);
+    mem_wait();
+    const uint32_t old = atomicAdd(st_cnt(&state[w]), 1u);
+    if (old + 1u != (uint32_t)G.indeg[w]) return;
+    const uint32_t acc = gld(st_acc(&state[w]));
+    const uint32_t cw = G.nodes[w].cta;
+    if (cw == src_cta) {
+      ready(acc, w, H);
+    } else if (cw < uni(lds()[kTeamNextCta])) {  // dispatched: ready at max(release, launch)
+      const uint32_t launch = gld(&cst[cw].launch), t = gld(&cst[cw].sm);
+      const uint32_t cyc = acc > launch ? acc : launch;
+      push(t, cyc, w);
+      atomicMin(lds() + red_next, cyc);  // its owner may have taken its minimum already
+    }
+  }
+  __device__ __forceinline__ void ready(uint32_t cyc, uint32_t v, uint32_t H) {
+    if (H)
+      push_own(cyc, v, H);
+    else
+      push(x, cyc, v);
+  }
+
+  // Releases of a node, the edges of `which` (1: released at issue, 2: at
+  // completion, 3: both), in two halves: the states of its inline successors
+  // set out before the node's stores (loads and stores return in order, so a
+  // load behind a store waits for it), and the releases once it is timed (s1:
+  // start + 1, f: finish, H as above).
+  struct Succ {
+    uint64_t sv[kInlineSucc];
+    bool sel[kInlineSucc], slow;
+  };
+  __device__ __forceinline__ Succ load_succ(const Rec& rec, uint32_t which) const {
+    const uint32_t nout = rec.nsucc();
+    Succ z;
+    z.slow = nout > kInlineSucc;
+#pragma unroll
+    for (uint32_t k = 0; k < kInlineSucc; ++k) {
+      const uint32_t bits = rec.succ(k) >> GTS_EDGE_KIND_SHIFT;
+      const bool at_issue = (bits & kDevOrder) && !ofin;
+      const bool in = k < nout;
+      z.slow |= in && (bits & kDevShared);
+      z.sel[k] = in && !(bits & kDevShared) && (which & (at_issue ? 1u : 2u)) != 0u;
+      z.sv[k] = 0;
+      // a node with one in-edge needs no state: this release readies it
+      if (z.sel[k] && rec.sindeg(k) != 1) z.sv[k] = state[rec.succ(k) & GTS_EDGE_TARGET_MASK];
+    }
+    return z;
+  }
+  __device__ __forceinline__ void release(const Rec& rec, const Succ& z, uint32_t which, uint32_t s1, uint32_t f,
+                                          uint32_t H) {
+#pragma unroll
+    for (uint32_t k = 0; k < kInlineSucc; ++k) {
+      if (!z.sel[k]) continue;
+      const uint32_t bits = rec.succ(k) >> GTS_EDGE_KIND_SHIFT, w = rec.succ(k) & GTS_EDGE_TARGET_MASK;
+      const uint32_t r = ((bits & kDevOrder) && !ofin) ? s1 : f;
+      const uint32_t cnt = (uint32_t)(z.sv[k] >> 32) + 1u;
+      uint32_t acc = (uint32_t)z.sv[k];
+      acc = r > acc ? r : acc;
+      if (cnt == rec.sindeg(k))
+        ready(acc, w, H);  // its state is not read again
+      else
+        state[w] = ((uint64_t)cnt << 32) | acc;
+    }
+    if (z.slow) release_more(rec, rec.nsucc(), which, s1, f, H);
+  }
+  // Successors beyond the inline three, four at a time (their entries, then
+  // in-degrees, then states in flight together; a node's successors are
+  // distinct), and inline ones into shared nodes.
+  __device__ __forceinline__ void release_more(const Rec& rec, uint32_t nout, uint32_t which, uint32_t s1, uint32_t f,
+                                               uint32_t H) {
+    for (uint32_t k = 0; k < kInlineSucc && k < nout; ++k) {
+      const uint32_t ent = rec.succ(k), bits = ent >> GTS_EDGE_KIND_SHIFT;
+      const bool at_issue = (bits & kDevOrder) && !ofin;
+      if ((bits & kDevShared) && (which & (at_issue ? 1u : 2u)))
+        release_shared(ent & GTS_EDGE_TARGET_MASK, at_issue ? s1 : f, rec.cta(), H);
+    }
+    const uint32_t base = t_n ? t_node0 + (rec.cta() - t_kc0) * t_n : 0u;
+    const gmem<const uint32_t>* sp = (const gmem<const uint32_t>*)(t_n ? G.tsucc : G.succ) + rec.sb();
+    const gmem<const uint16_t>* ip = (const gmem<const uint16_t>*)(t_n ? G.tindeg + t_base : G.indeg);
+    for (uint32_t k0 = kInlineSucc; k0 < nout; k0 += 4) {
+      uint32_t ent[4], ind[4];
+      uint64_t sv[4];
+      bool sel[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) ent[u] = k0 + u < nout ? sp[k0 + u] : 0u;
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        const bool at_issue = ((ent[u] >> GTS_EDGE_KIND_SHIFT) & kDevOrder) && !ofin;
+        sel[u] = k0 + u < nout && (which & (at_issue ? 1u : 2u)) != 0u;
+        ind[u] = sel[u] ? (uint32_t)ip[ent[u] & GTS_EDGE_TARGET_MASK] : 0u;
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        sv[u] = 0;
+        if (sel[u] && ind[u] != 1 && !((ent[u] >> GTS_EDGE_KIND_SHIFT) & kDevShared))
+          sv[u] = state[(ent[u] & GTS_EDGE_TARGET_MASK) + base];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        if (!sel[u]) continue;
+        const uint32_t bits = ent[u] >> GTS_EDGE_KIND_SHIFT, w = (ent[u] & GTS_EDGE_TARGET_MASK) + base;
+        const uint32_t r = ((bits & kDevOrder) && !ofin) ? s1 : f;
+        if (bits & kDevShared) {
+          release_shared(w, r, rec.cta(), H);
+          continue;
+        }
+        const uint32_t cnt = (uint32_t)(sv[u] >> 32) + 1u;
+        uint32_t acc = (uint32_t)sv[u];
+        acc = r > acc ? r : acc;
+        if (cnt == ind[u])
+          ready(acc, w, H);
+        else
+          state[w] = ((uint64_t)cnt << 32) | acc;
+      }
+    }
+  }
+
+  // ---- memory arrivals of this SM, in cycle order: RL entries in LDS, those
+  // behind them in scratch
+  __device__ __forceinline__ void ring_push(uint32_t cyc, uint32_t v, uint32_t op) {
+    if (gc == 0 && rc < RL) {
+      uint32_t p = rh + rc;
+      p = p >= RL ? p - RL : p;
+      rg_cyc[p * TH + x] = cyc;
+      rg_v[p * TH + x] = v;
+      rg_op[p * TH + x] = op;
+      ++rc;
+    } else if (gc < kRing) {
+      uint32_t* e = mq_g + (x * kRing + (gh + gc) % kRing) * kRingWords;
+      e[0] = v;
+      e[1] = cyc;
+      e[2] = op;
+      ++gc;
+    } else {
+      bad |= kBadQueue;
+    }
+  }
+  // d entries leave the front; the LDS part fills up again from scratch
+  __device__ __forceinline__ void ring_pop(uint32_t d) {
+    rh += d;
+    rh = rh >= RL ? rh - RL : rh;
+    rc -= d;
+    while (gc != 0 && rc < RL) {
+      const uint32_t* e = mq_g + (x * kRing + gh) * kRingWords;
+      uint32_t p = rh + rc;
+      p = p >= RL ? p - RL : p;
+      rg_cyc[p * TH + x] = e[1];
+      rg_v[p * TH + x] = e[0];
+      rg_op[p * TH + x] = e[2];
+      ++rc;
+      gh = (gh + 1u) % kRing;
+      --gc;
+    }
+  }
+
+  // The smallest due entry of the list, [0, nd).
+  __device__ __forceinline__ uint64_t smallest(uint32_t& at) const {
+    uint64_t best = ~0ull;
+    at = 0;
+    const uint32_t el = nd < QF ? nd : QF;
+    for (uint32_t i0 = 0; i0 < el; i0 += 4) {
+      uint64_t kk[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) kk[u] = q[(i0 + u < el ? i0 + u : el - 1u) * TH + x];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {  // past the end: the last entry again
+        const bool t = kk[u] < best;
+        best = t ? kk[u] : best;
+        at = t ? i0 + u : at;
+      }
+    }
+    for (uint32_t i0 = QF; i0 < nd; i0 += 4) {
+      uint64_t kk[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) kk[u] = q_g[((i0 + u < nd ? i0 + u : nd - 1u) - QF) * TH + x];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        const bool t = kk[u] < best;
+        best = t ? kk[u] : best;
+        at = t ? i0 + u : at;
+      }
+    }
+    return best;
+  }
+
+  // Issue the ready nodes of this SM with cycle < H, in (cycle, id) order;
+  // returns the steps this wave took.
+  __device__ __forceinline__ uint32_t local_phase(uint32_t H) {
+    n = q_cnt[x];
+    n = n < qcap ? n : qcap;
+    nd = 0;
+    mn = q_min[x];
+    if (mn < H) {  // due entries to the front
+      mn = kNone;
+      for (uint32_t i0 = 0; i0 < n; i0 += 4) {
+        uint64_t kk[4];  // a swap writes at or below the entry at hand
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) kk[u] = q_get(x, i0 + u < n ? i0 + u : n - 1u);
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) {
+          if (i0 + u >= n) continue;
+          const uint32_t c = (uint32_t)(kk[u] >> 32);
+          if (c < H) {
+            if (i0 + u != nd) {
+              q_set(x, i0 + u, q_get(x, nd));
+              q_set(x, nd, kk[u]);
+            }
+            ++nd;
+          } else {
+            mn = c < mn ? c : mn;
+          }
+        }
+      }
+    }
+    uint32_t steps = 0;
+    while (__ballot(nd != 0)) {
+      ++steps;
+      if (nd != 0) {
+        uint32_t at;
+        const uint64_t key = smallest(at);
+        const uint32_t t = (uint32_t)(key >> 32), v = (uint32_t)key;
+        const Rec rec = rec_of(v);
+        --nd;  // the last due entry takes its place, the last entry that one's
+        --n;
+        if (at != nd) q_set(x, at, q_get(x, nd));
+        if (nd != n) q_set(x, nd, q_get(x, n));
+        issue(t, v, rec, H);
+      }
+    }
+    q_cnt[x] = n;
+    q_min[x] = mn;
+    return steps;
+  }
+
+  // Timing on the SM's servers: the node holds its class's subpartition lanes
+  // (compute), the shared-memory pipe or the global-memory engine (memory
+  // nodes; L2 / DRAM follow in the memory phase), SYNC nothing; every held
+  // server becomes free at start + occupancy.
+  __device__ __forceinline__ void issue(uint32_t t, uint32_t v, const Rec& rec, uint32_t H) {
+    const uint32_t op = rec.op();
+    const uint4 od = optab[op];
+    const uint32_t cls = od.w & 7u;
+    const bool comp = cls <= C_SFU, is_mem = cls == C_GLOAD || cls == C_GSTORE;
+    const bool book = !is_mem && !mem_only && !sink_ret;
+    const uint32_t which = is_mem ? 1u : 3u;
+    const Succ z = load_succ(rec, which);
+    uint4 cs = make_uint4(0, 0, 0, 0);
+    if (book) cs = *reinterpret_cast<const uint4*>(&cst[rec.cta()]);
+    uint32_t* Sv = srv + (comp ? (od.w >> 16) : smem_w + (is_mem ? 1u : 0u)) * TH + x;
+    uint32_t st = t;
+    if (nsub == 1u || !comp) {
+      if (cls != C_SYNC) {
+        const uint32_t a = nocont ? 0u : Sv[0];
+        st = a > st ? a : st;
+      }
+    } else if (!nocont) {
+      for (uint32_t l = 0; l < nsub; ++l) {
+        const uint32_t a = Sv[l * TH];
+        st = (od.w >> (8u + l)) & 1u && a > st ? a : st;
+      }
+    }
+    const uint64_t fr = (uint64_t)st + od.x;
+    const uint64_t f = fr + (is_mem ? 0u : od.z);
+    if (f > kMaxCycle) {
+      bad |= kBadOverflow;
+      return;
+    }
+    if (nsub == 1u || !comp) {
+      if (cls != C_SYNC) Sv[0] = (uint32_t)fr;
+    } else {
+      for (uint32_t l = 0; l < nsub; ++l)
+        if ((od.w >> (8u + l)) & 1u) Sv[l * TH] = (uint32_t)fr;
+    }
+    ++n_issued;
+    if (is_mem) ring_push(st, v, op);
+    release(rec, z, which, st + 1u, (uint32_t)f, H);
+    if (!is_mem) record(v, st, (uint32_t)f);
+    if (book) {  // a compute node never completes its CTA
+      const uint32_t mf = (uint32_t)f > cs.w ? (uint32_t)f : cs.w;
+      *reinterpret_cast<uint2*>(&cst[rec.cta()].left) = make_uint2(cs.z - 1u, mf);
+    }
+  }
+
+  // A memory node finishes at f: outputs, CTA bookkeeping, releases.
+  __device__ __forceinline__ void complete(uint32_t v, uint32_t s, uint32_t f, const Rec& rec) {
+    const Succ z = load_succ(rec, 2u);
+    uint4 cs = make_uint4(0, 0, 0, 0);
+    if (!sink_ret) cs = *reinterpret_cast<const uint4*>(&cst[rec.cta()]);
+    release(rec, z, 2u, 0u, f, 0u);
+    record(v, s, f);
+    if (sink_ret) {
+      if ((rec.b.w >> 16) & kRecSink) ret_push(f);  // the sink finishes last
+    } else {
+      const uint32_t left = cs.z - 1u;
+      const uint32_t mf = f > cs.w ? f : cs.w;
+      *reinterpret_cast<uint2*>(&cst[rec.cta()].left) = make_uint2(left, mf);
+      if (left == 0) ret_push(mf);  // the CTA retires at its largest finish
+    }
+  }
+
+  // The ordered batch (M arrivals, position lane * E + r) through the servers:
+  // the end of each one's memory service to LDS, for the slots of this wave.
+  template <uint32_t E>
+  __device__ __forceinline__ void serve(uint32_t M, uint32_t base, uint32_t cnt) {
+    const uint4* const srt = reinterpret_cast<const uint4*>(lds() + kTeamSorted);
+    uint32_t* const mend = lds() + kTeamMend;
+    double cyc[E], occ[E];
+    uint32_t sl[E];
+    bool in[E], dram[E];
+    bool any_l2 = false, any_dr = false;
+#pragma unroll
+    for (uint32_t r = 0; r < E; ++r) {
+      const uint32_t p = lane * E + r;
+      in[r] = p < M;
+      const uint4 e = srt[in[r] ? p : 0u];
+      cyc[r] = (double)e.x;
+      occ[r] = (double)e.z;
+      sl[r] = e.y & 0x7FFFFFFFu;
+      dram[r] = (e.y >> 31) != 0u;
+      any_l2 |= in[r] && !dram[r];
+      any_dr |= in[r] && dram[r];
+    }
+#pragma unroll
+    for (uint32_t d = 0; d < 2; ++d) {
+      if (!__ballot(d ? any_dr : any_l2)) continue;
+      double& av = d ? dram_av : l2_av;
+      MaxPlus f{kNegInf, 0.0};
+#pragma unroll
+      for (uint32_t r = 0; r < E; ++r)
+        if (in[r] && dram[r] == (d != 0)) f = after(f, MaxPlus{cyc[r], occ[r]});
+      const MaxPlus inc = wave_incl_mp(f);
+      const MaxPlus exc = dpp_mp<kWaveShr1>(inc);
+      double y = __builtin_fmax(av, exc.a) + exc.o;
+      if (!nocont) av = __builtin_fmax(av, lane_f64(inc.a, 63)) + lane_f64(inc.o, 63);
+#pragma unroll
+      for (uint32_t r = 0; r < E; ++r)
+        if (in[r] && dram[r] == (d != 0)) {
+          const double m = nocont ? cyc[r] : __builtin_fmax(y, cyc[r]);
+          y = m + occ[r];
+          if (sl[r] - base < cnt) mend[sl[r]] = (uint32_t)__builtin_fmin(y, 4294967295.0);
+        }
+    }
+    wsync();
+  }
+
+  // ---- dispatch at cycle t (first wave only): up to 64 CTAs at a time are
+  // placed on SMs (most free slots, lowest id), then set up by one lane each
+  __device__ __forceinline__ void dispatch(uint32_t t) {
+    uint32_t* const ctl = lds() + kTeamCtl;
+    uint32_t next_cta = uni(ctl[0]), cur_k = uni(ctl[2]), k_begin = uni(ctl[3]), k_end = uni(ctl[4]);
+    const uint32_t retired = uni(ctl[1]);
+    if (next_cta >= G.n_ctas) return;
+    uint32_t kstart_k = uni(ctl[5]), kstart_t = uni(ctl[6]);
+    uint64_t slots = uni64(*reinterpret_cast<const uint64_t*>(ctl + 8));
+    while (next_cta < G.n_ctas) {
+      while (next_cta >= k_end) {
+        ++cur_k;
+        const KernelDev kd = G.kernels[cur_k];
+        k_begin = uni(kd.cta_begin);
+        k_end = uni(kd.cta_end);
+        slots = uni64(kernel_slots(kd, hw));
+      }
+      if (retired < k_begin) break;  // the previous kernel is still running
+      // every CTA before next_cta is dispatched and `retired` of them have
+      // retired, all of the running kernel: its free slots are known
+      const uint64_t cap = (uint64_t)nsm * slots, busy = next_cta - retired;
+      const uint64_t room = cap > busy ? cap - busy : 0u;
+      uint32_t lim = k_end - next_cta < 64u ? k_end - next_cta : 64u;
+      lim = room < lim ? (uint32_t)room : lim;
+      if (lim == 0) break;
+      // the records of the CTAs to place, in flight during the placement
+      const uint32_t c = next_cta + lane;
+      uint4 c0 = make_uint4(0, 0, 0, 0), c1 = make_uint4(0, 0, 0, 0);
+      if (lane < lim) {
+        const gmem<const uint32_t>* p = (const gmem<const uint32_t>*)(G.ctas + c);
+        c0 = ld4(p);      // node_begin, node_count, root_begin, root_count
+        c1 = ld4(p + 4);  // memory nodes, first three roots
+      }
+      // an SM's key: fewest resident CTAs, then lowest id; 0 when full
+      uint32_t rs[NW], key[NW], mysm = 0;
+      auto key_of = [&](uint32_t j) {
+        const uint32_t s = lane * NW + j;
+        return s < nsm && rs[j] < slots ? ((0xFFFFFFu - rs[j]) << 8) | (255u - s) : 0u;
+      };
+#pragma unroll
+      for (uint32_t j = 0; j < NW; ++j) {
+        rs[j] = res[lane + 64u * j];
+        key[j] = key_of(j);
+      }
+      uint32_t k = 0;
+      while (k < lim) {
+        uint32_t best = key[0];
+#pragma unroll
+        for (uint32_t j = 1; j < NW; ++j) best = key[j] > best ? key[j] : best;
+        best = wave_max_u32(best);
+        if (best == 0) break;  // every SM is full
+        const uint32_t s = 255u - (best & 255u);
+        if (lane == k) mysm = thread_of(s);
+#pragma unroll
+        for (uint32_t j = 0; j < NW; ++j) {
+          rs[j] += key[j] == best ? 1u : 0u;
+          key[j] = key_of(j);
+        }
+        ++k;
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < NW; ++j) res[lane + 64u * j] = rs[j];
+      if (k == 0) break;
+      if (run_k != cur_k) load_template(cur_k);  // the first CTAs of a kernel: it is now the running one
+      if (kstart_k != cur_k) {
+        kstart_k = cur_k;
+        kstart_t = t;
+      }
+      const uint64_t launch = (uint64_t)t + hw[HW_CTALAT] + (kstart_t == t ? hw[HW_KLAT] : 0u);
+      if (launch > kMaxCycle) {
+        bad |= kBadOverflow;
+        break;
+      }
+      if (lane < k && !sink_ret)  // a CTA that retires with its sink keeps no state
+        *reinterpret_cast<uint4*>(&cst[c]) = make_uint4(mysm, (uint32_t)launch, mem_only ? c1.x : c0.y, 0u);
+      // zero the node state of unshared CTAs (shared ones were zeroed at start)
+      for (uint32_t j = 0; j < k; ++j) {
+        const uint32_t nb = lane_u32(c0.x, (int)j), nc = lane_u32(c0.y, (int)j), fl = lane_u32(c0.w, (int)j);
+        if (!(fl & kCtaShared))
+          for (uint32_t i = lane; i < nc; i += 64) state[nb + i] = 0ull;
+      }
+      if (lane < k) {
+        const bool shared = (c0.w & kCtaShared) != 0;
+        const uint32_t nroots = c0.w & ~kCtaShared;
+        for (uint32_t r = 0; r < nroots; ++r) {
+          const uint32_t v = r == 0 ? c1.y : r == 1 ? c1.z : r == 2 ? c1.w : G.roots[c0.z + r];
+          if (!shared) {  // no in-edges at all
+            push(mysm, (uint32_t)launch, v);
+          } else {
+            const uint64_t sv = gld(&state[v]);
+            if ((uint32_t)(sv >> 32) == (uint32_t)G.indeg[v]) {
+              const uint32_t acc = (uint32_t)sv;
+              push(mysm, acc > launch ? acc : (uint32_t)launch, v);
+            }
+          }
+        }
+      }
+      next_cta += k;
+      wsync();
+    }
+    if (lane == 0) {
+      ctl[0] = next_cta;
+      ctl[2] = cur_k;
+      ctl[3] = k_begin;
+      ctl[4] = k_end;
+      ctl[5] = kstart_k;
+      ctl[6] = kstart_t;
+      *reinterpret_cast<uint64_t*>(ctl + 8) = slots;
+      ctl[10] = run_k;
+    }
+    wsync();
+  }
+
+  // ---- retirement phase (first wave only): retirements below H, in cycle
+  // order, each distinct cycle followed by dispatch.  More than kTeamCap of
+  // them lower H; the new H goes to LDS.
+  __device__ __forceinline__ void retire(uint32_t T, uint32_t H) {
+    uint32_t* const ctl = lds() + kTeamCtl;
+    uint64_t* const due_l = reinterpret_cast<uint64_t*>(lds() + kTeamKey);
+    uint32_t cnt = uni(lds()[kTeamRetCnt]);
+    cnt = cnt < kRetireCap ? cnt : kRetireCap;
+    auto below = [&](uint32_t X) {
+      uint32_t c = 0;
+      for (uint32_t i = lane; i < cnt; i += 64) c += (uint32_t)(ret_get(i) >> 32) < X;
+      return wave_sum_u32(c);
+    };
+    uint32_t D = below(H);
+    if (D > kTeamCap) {
+      uint32_t lo = T + 1u, hi = H;
+      while (hi - lo > 1u) {
+        const uint32_t mid = lo + (hi - lo) / 2u;
+        if (below(mid) <= kTeamCap)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      H = lo;
+      D = below(H);
+    }
+    // more than kTeamCap at cycle T alone: released together
+    const bool single = D > kTeamCap;
+    uint32_t dp = 0, kp = 0, kmin = kNone;
+    for (uint32_t base = 0; base < cnt; base += 64) {
+      const uint32_t i = base + lane;
+      const uint64_t k = i < cnt ? ret_get(i) : ~0ull;
+      const bool due = i < cnt && (uint32_t)(k >> 32) < H;
+      const bool keep = i < cnt && !due;
+      const uint64_t bd = __ballot(due), bk = __ballot(keep);
+      if (due) {
+        if (single)
+          atomicSub(&res[(uint32_t)k], 1u);
+        else
+          due_l[dp + lanes_below(bd, lane)] = k;
+      }
+      if (keep) {
+        const uint32_t dst = kp + lanes_below(bk, lane);
+        if (dst != i) ret_set(dst, k);
+        kmin = (uint32_t)(k >> 32) < kmin ? (uint32_t)(k >> 32) : kmin;
+      }
+      dp += (uint32_t)__popcll(bd);
+      kp += (uint32_t)__popcll(bk);
+    }
+    kmin = wave_min_u32(kmin);
+    wsync();
+    if (lane == 0) {
+      lds()[kTeamRetCnt] = kp;
+      lds()[kTeamRetMin] = kmin;
+      ctl[11] = H;
+    }
+    uint32_t retired = uni(ctl[1]);
+    if (single) {
+      retired += dp;
+      if (lane == 0) ctl[1] = retired;
+      wsync();
+      dispatch(T);
+      return;
+    }
+    // up to kTeamCap due ones, four per lane; the earliest cycle each time
+    uint32_t rcyc[kTeamCap / 64], rx[kTeamCap / 64];
+#pragma unroll
+    for (uint32_t u = 0; u < kTeamCap / 64; ++u) {
+      const uint32_t i = u * 64u + lane;
+      const uint64_t k = i < dp ? due_l[i] : ~0ull;
+      rcyc[u] = (uint32_t)(k >> 32);
+      rx[u] = (uint32_t)k;
+    }
+    while (dp) {
+      uint32_t m = rcyc[0];
+#pragma unroll
+      for (uint32_t u = 1; u < kTeamCap / 64; ++u) m = rcyc[u] < m ? rcyc[u] : m;
+      m = wave_min_u32(m);
+      uint32_t c = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < kTeamCap / 64; ++u) {
+        const bool now = rcyc[u] == m;
+        if (now) {
+          atomicSub(&res[rx[u]], 1u);
+          rcyc[u] = kNone;
+        }
+        c += (uint32_t)__popcll(__ballot(now));
+      }
+      dp -= c;
+      retired += c;
+      wsync();
+      if (lane == 0) ctl[1] = retired;
+      wsync();
+      dispatch(m);
+      if (__ballot(bad != 0)) break;
+    }
+  }
+};
+
+template <uint32_t NW>
+__device__ __forceinline__ void team_body(const Launch& L) {
+  constexpr uint32_t TH = 64u * NW, GQ = kTeamHeads;
+  const uint32_t b = blockIdx.x;
+  if (b >= L.B) return;
+  uint32_t* const lds = team_lds_words;
+  TSim<NW> S;
+  S.G = L.img;
+  S.hw = L.hw + (uint64_t)b * HW_WORDS;
+  S.b = b;
+  S.x = threadIdx.x;
+  S.lane = S.x & 63u;
+  S.wave = uni(S.x >> 6);
+  S.nocont = (L.flags & GTS_NO_CONTENTION) != 0;
+  S.ofin = (L.flags & GTS_ORDER_AT_FINISH) != 0;
+  S.mem_only = (L.img.props & kGraphComputeFeedsData) != 0;
+  S.want_digest = L.out_digest != nullptr;
+  S.nsm = S.hw[HW_NSM];
+  S.nsub = L.srv_one ? 1u : S.hw[HW_NSUB];
+  const uint32_t sstride = server_stride(S.G.props, S.nsub);
+  S.smem_w = sstride - 2u;
+  S.QF = L.qp;
+  S.RL = L.team_ring;
+  S.retl = L.team_ret;
+  S.qcap = S.QF + kPoolSpill * 64u / TH;
+  const uint32_t x = S.x, lane = S.lane;
+  uint8_t* sim = L.sims + (uint64_t)b * L.layout.stride;
+  S.state = reinterpret_cast<uint64_t*>(sim + L.layout.off_state);
+  S.cst = reinterpret_cast<CtaState*>(sim + L.layout.off_cta);
+  S.mq_g = reinterpret_cast<uint32_t*>(sim + L.layout.off_mq);
+  S.q_g = (gmem<uint64_t>*)(sim + L.layout.off_rp);
+  S.ret_g = (gmem<uint64_t>*)(sim + L.layout.off_ret);
+  const TeamLds W = team_lds(TH, S.G.n_ops + S.G.n_tops, server_stride(S.G.props, L.srv_one ? 1u : L.max_nsub), L.qp,
+                             L.team_ring, L.team_ret);
+  S.optab = reinterpret_cast<uint4*>(lds + W.optab);
+  S.srv = lds + W.srv;
+  S.q_cnt = lds + W.q_cnt;
+  S.q_min = lds + W.q_min;
+  S.res = lds + W.res;
+  S.q = reinterpret_cast<uint64_t*>(lds + W.q);
+  S.rg_cyc = lds + W.ring;
+  S.rg_v = S.rg_cyc + S.RL * TH;
+  S.rg_op = S.rg_v + S.RL * TH;
+  S.ret_l = reinterpret_cast<uint64_t*>(lds + W.ret);
+  S.out_cycles = (L.flags & GTS_OUT_NODES) ? L.out_cycles : nullptr;
+  uint64_t* const w_key = reinterpret_cast<uint64_t*>(lds + kTeamKey);
+  uint32_t* const w_op = lds + kTeamOp;
+  uint4* const srt = reinterpret_cast<uint4*>(lds + kTeamSorted);
+  uint32_t* const ctl = lds + kTeamCtl;
+
+  // a kernel whose CTA fits nowhere makes the simulation infeasible
+  bool infeasible = false;
+  for (uint32_t k = lane; k < S.G.n_kernels; k += 64) infeasible |= kernel_slots(S.G.kernels[k], S.hw) == 0;
+  if (__ballot(infeasible)) {  // every wave sees the same
+    if (x == 0) {
+      L.out_makespan[b] = 0xFFFFFFFFu;
+      L.out_status[b] = GTS_SIM_INFEASIBLE;
+      if (L.out_digest) L.out_digest[b] = 0;
+    }
+    return;
+  }
+
+  // Setup: duration table (every wave goes through all of it for the
+  // smallest delays, thread x writes entries x, x + TH, ...), idle servers,
+  // empty queues.
+  uint64_t lm_l2 = ~0ull, lm_dr = ~0ull;
+  for (uint32_t p = lane; p < S.G.n_ops; p += 64) {
+    uint4 e = op_entry(S.G.ops[p], S.hw, S.G.props);
+    const uint32_t cls = e.w & 7u;
+    if (L.srv_one && cls <= C_SFU)  // the class's single word: lane 0 of its slot
+      e.w = (e.w & 0xFFu) | (1u << 8) | (compute_slot(S.G.props, cls) << 16);
+    if ((p >> 6) % NW == S.wave) S.optab[p] = e;
+    if (cls == C_GLOAD || cls == C_GSTORE) {
+      const uint64_t d = (uint64_t)e.y + e.z;
+      uint64_t& lm = (e.w >> 3) & 1u ? lm_dr : lm_l2;
+      lm = d < lm ? d : lm;
+    }
+  }
+  lm_l2 = wmin64(lm_l2);
+  lm_dr = wmin64(lm_dr);
+  const double dmin_l2 = lm_l2 == ~0ull ? __builtin_inf() : (double)lm_l2;
+  const double dmin_dr = lm_dr == ~0ull ? __builtin_inf() : (double)lm_dr;
+  for (uint32_t i = 0; i < sstride; ++i) S.srv[i * TH + x] = 0;
+  S.q_cnt[x] = 0;
+  S.q_min[x] = kNone;
+  S.res[x] = 0;
+  if (x < kTeamFixedInit) lds[kTeamCtl + x] = 0;
+  __syncthreads();
+  for (uint32_t p = x; p < S.G.n_tops; p += TH) S.optab[S.G.n_ops + p] = S.optab[S.G.tops[p]];
+  if (x == 0) {
+    const KernelDev kd = S.G.kernels[0];
+    ctl[3] = kd.cta_begin;
+    ctl[4] = kd.cta_end;
+    ctl[5] = kNone;  // no kernel has started
+    *reinterpret_cast<uint64_t*>(ctl + 8) = kernel_slots(kd, S.hw);
+    ctl[10] = kNone;
+    lds[kTeamRetMin] = kNone;
+    for (uint32_t i = 0; i < 4; ++i) lds[kTeamRed + i] = kNone;
+  }
+  if (S.G.props & kGraphHasShared) {
+    for (uint32_t c = x; c < S.G.n_ctas; c += TH) {
+      const CtaDev cd = S.G.ctas[c];
+      if (cd.root_count & kCtaShared)
+        for (uint32_t i = 0; i < cd.node_count; ++i) S.state[cd.node_begin + i] = 0ull;
+    }
+  }
+  S.run_k = kNone;  // no CTA dispatched yet
+  S.t_n = 0;
+  S.sink_ret = false;
+  S.l2_av = 0.0;
+  S.dram_av = 0.0;
+  S.rh = S.rc = S.gh = S.gc = 0;
+  S.digest = 0;
+  S.makespan = 0;
+  S.nfin = 0;
+  S.bad = 0;
+  S.n_issued = 0;
+  const bool clk = L.clocks != 0;
+  uint64_t ck[5] = {0, 0, 0, 0, 0};
+  uint32_t windows = 0, steps = 0, arrivals = 0, most = 0;
+  uint32_t rb = 0;  // which half of the exchange words is next
+
+  // Per-wave counts (and the smallest key bound) across the workgroup.
+  auto exchange = [&](uint32_t cnt, uint64_t kb, uint32_t& total, uint32_t& base) -> uint64_t {
+    uint32_t* const e = lds + kTeamExch + rb * 16u;
+    rb ^= 1u;
+    if constexpr (NW > 1) {
+      if (lane == 0) *reinterpret_cast<uint4*>(e + S.wave * 4u) = make_uint4(cnt, (uint32_t)kb, (uint32_t)(kb >> 32), 0u);
+      lds_barrier<NW>();
+      total = base = 0;
+      uint64_t k = ~0ull;
+#pragma unroll
+      for (uint32_t w = 0; w < NW; ++w) {
+        const uint4 v = *reinterpret_cast<const uint4*>(e + w * 4u);
+        const uint64_t kw = ((uint64_t)v.z << 32) | v.y;
+        total += v.x;
+        base += w < S.wave ? v.x : 0u;
+        k = kw < k ? kw : k;
+      }
+      total = uni(total);
+      base = uni(base);
+      return uni64(k);
+    } else {
+      total = cnt;
+      base = 0;
+      return kb;
+    }
+  };
+
+  __syncthreads();
+  if (S.wave == 0) S.dispatch(0);
+  __syncthreads();
+  if (uni(ctl[10]) != S.run_k) S.load_template(uni(ctl[10]));
+
+  while (true) {
+    const uint64_t c0 = clk ? __builtin_amdgcn_s_memtime() : 0ull;
+    // T: the earliest pending event.  Each wave's minimum goes to this
+    // window's words {ready or arrival, retirement}, which pushes to other
+    // SMs lower as well.
+    const uint32_t par = (windows & 1u) * 2u;
+    {
+      uint32_t m = S.q_min[x];
+      if (S.rc) {
+        const uint32_t h = S.rg_cyc[S.rh * TH + x];
+        m = h < m ? h : m;
+      }
+      m = wave_min_u32(m);
+      const bool any_bad = __ballot(S.bad != 0) != 0;
+      if (lane == 0) {
+        atomicMin(&lds[kTeamRed + par], m);
+        if (S.wave == 0) atomicMin(&lds[kTeamRed + par + 1u], lds[kTeamRetMin]);
+        if (any_bad) atomicOr(&ctl[12], 1u);
+      }
+    }
+    lds_barrier<NW>();
+    const uint32_t rmin = uni(lds[kTeamRed + par + 1u]);
+    uint32_t T = uni(lds[kTeamRed + par]);
+    if (uni(ctl[12])) break;
+    T = rmin < T ? rmin : T;
+    if (T == kNone) break;  // cycles stop at kMaxCycle
+    S.red_next = kTeamRed + (par ^ 2u);
+    if (x == 0) {
+      lds[S.red_next] = kNone;
+      lds[S.red_next + 1u] = kNone;
+      lds[kTeamRetMin] = rmin;
+    }
+    ++windows;
+    // H: no arrival of this window completes before it.  An arrival waits
+    // for its server, so a busy server's backlog lengthens the window.
+    uint32_t H;
+    {
+      const double t = (double)T;
+      const double a = S.nocont ? t : __builtin_fmax(t, S.l2_av), d = S.nocont ? t : __builtin_fmax(t, S.dram_av);
+      double h = __builtin_fmin(a + dmin_l2, d + dmin_dr);
+      h = __builtin_fmin(h, t + (double)kWindowMax);
+      H = uni((uint32_t)__builtin_fmin(h, 4294967295.0));
+    }
+    const uint64_t c1 = clk ? __builtin_amdgcn_s_memtime() : 0ull;
+    if (rmin < H) {
+      if (S.wave == 0) S.retire(T, H);
+      __syncthreads();
+      H = uni(ctl[11]);
+      if (uni(ctl[10]) != S.run_k) S.load_template(uni(ctl[10]));
+    }
+    const uint64_t c2 = clk ? __builtin_amdgcn_s_memtime() : 0ull;
+    steps += S.local_phase(H);
+    const uint64_t c3 = clk ? __builtin_amdgcn_s_memtime() : 0ull;
+
+    // Memory phase: the arrivals whose key (cycle, id) is below K <= H << 32,
+    // at most kTeamCap of them, from the first GQ of each SM's ring.
+    uint32_t ec[GQ], ev[GQ], eo[GQ];
+    uint64_t kb = (uint64_t)H << 32;
+    const uint32_t ld = S.rc < GQ ? S.rc : GQ;
+#pragma unroll
+    for (uint32_t u = 0; u < GQ; ++u) {
+      ec[u] = kNone;
+      ev[u] = eo[u] = 0;
+      if (u < ld) {
+        uint32_t p = S.rh + u;
+        p = p >= S.RL ? p - S.RL : p;
+        ec[u] = S.rg_cyc[p * TH + x];
+        ev[u] = S.rg_v[p * TH + x];
+        eo[u] = S.rg_op[p * TH + x];
+        if (u + 1u == ld && S.rc + S.gc > ld) {
+          const uint64_t k = (((uint64_t)ec[u] << 32) | ev[u]) + 1u;
+          kb = k < kb ? k : kb;
+        }
+      }
+    }
+    auto due = [&](uint64_t K) -> uint32_t {
+      uint32_t c = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < GQ; ++u) c += (((uint64_t)ec[u] << 32) | ev[u]) < K;
+      return c;
+    };
+    uint64_t K = (uint64_t)H << 32;
+    uint32_t d = due(K), M, wbase;
+    const uint64_t cut = __ballot(kb < K) ? wmin64(kb) : K;
+    uint32_t cw = wave_sum_u32(d);
+    const uint64_t Kx = exchange(cw, cut, M, wbase);
+    if (Kx < K) {  // some SM has more arrivals than were loaded
+      K = Kx;
+      d = due(K);
+      cw = wave_sum_u32(d);
+      exchange(cw, 0, M, wbase);
+    }
+    if (M > kTeamCap) {
+      // the largest cycle boundary that keeps kTeamCap, or, when cycle T
+      // alone holds more, a boundary between the keys of cycle T
+      const uint64_t Kmax = K;
+      auto count = [&](uint64_t k) -> uint32_t {
+        uint32_t m, wb;
+        exchange(wave_sum_u32(due(k)), 0, m, wb);
+        return m;
+      };
+      uint64_t lo = T, hi = Kmax >> 32;
+      if (count(hi << 32) <= kTeamCap) {
+        lo = hi;
+      } else {
+        while (hi - lo > 1) {
+          const uint64_t mid = lo + (hi - lo) / 2;
+          if (count(mid << 32) <= kTeamCap)
+            lo = mid;
+          else
+            hi = mid;
+        }
+      }
+      K = lo << 32;
+      if (lo == T) {
+        uint64_t klo = (uint64_t)T << 32, khi = ((uint64_t)T + 1) << 32;
+        khi = Kmax < khi ? Kmax : khi;
+        while (khi - klo > 1) {
+          const uint64_t mid = klo + (khi - klo) / 2;
+          if (count(mid) <= kTeamCap)
+            klo = mid;
+          else
+            khi = mid;
+        }
+        K = klo;
+      }
+      d = due(K);
+      cw = wave_sum_u32(d);
+      exchange(cw, 0, M, wbase);
+    }
+    const uint64_t c4 = clk ? __builtin_amdgcn_s_memtime() : 0ull;
+    if (M) {
+      const uint32_t p = wbase + wave_excl_scan_u32(d);
+#pragma unroll
+      for (uint32_t u = 0; u < GQ; ++u)
+        if (u < d) {
+          w_key[p + u] = ((uint64_t)ec[u] << 32) | ev[u];
+          w_op[p + u] = eo[u];
+        }
+      if (x == 0)
+        for (uint32_t i = 0; i < 8; ++i) w_key[M + i] = ~0ull;  // the count reads eight keys at a time
+      if (d) S.ring_pop(d);
+      lds_barrier<NW>();
+      for (uint32_t i = x; i < M; i += TH) {
+        const uint64_t mine = w_key[i];
+        const uint4 od = S.optab[w_op[i]];
+        uint32_t r = 0;
+        for (uint32_t j = 0; j < M; j += 8) {
+          uint4 kk[4];
+#pragma unroll
+          for (uint32_t u = 0; u < 4; ++u) kk[u] = *reinterpret_cast<const uint4*>(w_key + j + 2u * u);
+#pragma unroll
+          for (uint32_t u = 0; u < 4; ++u) {
+            r += (((uint64_t)kk[u].y << 32) | kk[u].x) < mine ? 1u : 0u;
+            r += (((uint64_t)kk[u].w << 32) | kk[u].z) < mine ? 1u : 0u;
+          }
+        }
+        srt[r] = make_uint4((uint32_t)(mine >> 32), i | ((od.w >> 3) & 1u) << 31, od.y, 0u);
+      }
+      lds_barrier<NW>();
+      if (M <= 64)
+        S.template serve<1>(M, wbase, cw);
+      else if (M <= 128)
+        S.template serve<2>(M, wbase, cw);
+      else
+        S.template serve<4>(M, wbase, cw);
+#pragma unroll
+      for (uint32_t u = 0; u < GQ; ++u) {
+        if (!__ballot(u < d)) break;
+        if (u < d) {
+          const uint4 od = S.optab[eo[u]];
+          const Rec rec = S.rec_of(ev[u]);
+          const uint64_t e = (uint64_t)ec[u] + od.x, m = lds[kTeamMend + p + u];
+          const uint64_t f = (e > m ? e : m) + od.z;
+          if (f > kMaxCycle)
+            S.bad |= kBadOverflow;
+          else
+            S.complete(ev[u], ec[u], (uint32_t)f, rec);
+        }
+      }
+      arrivals += M;
+      most = M > most ? M : most;
+    }
+    if (clk) {
+      const uint64_t c5 = __builtin_amdgcn_s_memtime();
+      ck[0] += c1 - c0;
+      ck[1] += c2 - c1;
+      ck[2] += c3 - c2;
+      ck[3] += c4 - c3;
+      ck[4] += c5 - c4;
+    }
+  }
+
+  // Results: per-wave sums, then the first wave's lane adds them up.
+  uint64_t dg = S.digest;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) dg += __shfl_xor(dg, o, 64);
+  const uint32_t mk = wave_max_u32(S.makespan);
+  const uint32_t nf = wave_sum_u32(S.nfin), ni = wave_sum_u32(S.n_issued);
+  const bool queue = __ballot((S.bad & kBadQueue) != 0) != 0, ovf = __ballot((S.bad & kBadOverflow) != 0) != 0;
+  __syncthreads();
+  uint32_t* const fin = lds + kTeamSorted;
+  if (lane == 0) {
+    uint32_t* const e = fin + S.wave * 8u;
+    e[0] = (uint32_t)dg;
+    e[1] = (uint32_t)(dg >> 32);
+    e[2] = mk;
+    e[3] = nf;
+    e[4] = ni;
+    e[5] = (queue ? 1u : 0u) | (ovf ? 2u : 0u);
+  }
+  __syncthreads();
+  if (x == 0) {
+    uint64_t dsum = 0;
+    uint32_t mmax = 0, fsum = 0, isum = 0, why = 0;
+    for (uint32_t w = 0; w < NW; ++w) {
+      const uint32_t* const e = fin + w * 8u;
+      dsum += ((uint64_t)e[1] << 32) | e[0];
+      mmax = e[2] > mmax ? e[2] : mmax;
+      fsum += e[3];
+      isum += e[4];
+      why |= e[5];
+    }
+    uint64_t* stats = reinterpret_cast<uint64_t*>(sim + L.layout.stride - kStatsBytes);
+    stats[0] = windows;
+    stats[1] = steps;
+    stats[2] = isum;
+    stats[3] = arrivals;
+    stats[4] = ctl[1];
+    stats[5] = most;
+    for (uint32_t i = 0; i < 5; ++i) stats[6 + i] = ck[i];
+    stats[11] = NW;  // wavefronts of the simulation
+    stats[12] = why;
+    stats[13] = stats[14] = stats[15] = 0;
+    int32_t st = GTS_SIM_OK;
+    if (why & 1u)
+      st = kStatusRetry;
+    else if (why & 2u)
+      st = GTS_SIM_OVERFLOW;
+    else if (fsum != S.G.n_nodes)
+      st = GTS_SIM_DEADLOCK;
+    L.out_status[b] = st;
+    L.out_makespan[b] = st == GTS_SIM_OK ? mmax : 0xFFFFFFFFu;
+    if (L.out_digest) L.out_digest[b] = st == GTS_SIM_OK ? dsum : 0ull;
+  }
+}
+
+}  // namespace
+
+extern "C" __global__ __launch_bounds__(64) void gts_sim_team1(Launch L) { team_body<1>(L); }
+extern "C" __global__ __launch_bounds__(128) void gts_sim_team2(Launch L) { team_body<2>(L); }
+extern "C" __global__ __launch_bounds__(192) void gts_sim_team3(Launch L) { team_body<3>(L); }
+extern "C" __global__ __launch_bounds__(256) void gts_sim_team4(Launch L) { team_body<4>(L); }
+
+hipError_t launch_team(const Launch& L, uint32_t lds_bytes, hipStream_t stream) {
+  if (L.B == 0) return hipSuccess;
+  const uint32_t nw = (L.max_nsm + 63) / 64;
+  void (*const k[4])(Launch) = {gts_sim_team1, gts_sim_team2, gts_sim_team3, gts_sim_team4};
+  hipLaunchKernelGGL(k[nw - 1u], dim3(L.B), dim3(64u * nw), lds_bytes, stream, L);
+  return hipGetLastError();
+}
+
+}  // namespace gts

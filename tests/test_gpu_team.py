@@ -1,0 +1,116 @@
+"""GPU parity of the team kernel on its own (one workgroup per simulation, one
+thread per SM): random graphs the windowed kernels accept, named workloads
+and batches at the edges of its lists, shown to have run on it, bit-exact
+against the oracle; and the hand-back of a simulation that overflows them."""
+import numpy as np
+import pytest
+
+from paper_2607_11262_amd import api
+from paper_2607_11262_amd.gen import hw as H
+from paper_2607_11262_amd.gen import workloads as W
+from paper_2607_11262_amd.gen.rng import SplitMix64
+from test_gpu_windowed import (ALL, STATS_BYTES, STATUS_RETRY, _simultaneous_loads_graph, _wide_roots_graph, compare,
+                               note)
+from windowed import window_eligible, windowed_graph, windowed_machines
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch
+
+
+def run_team_only(torch, g, hws, flags, monkeypatch):
+    """As run_window_only, with GTS_KERNEL=team; returns the outputs and, per
+    simulation, the windows and the wavefronts its counter block reports."""
+    monkeypatch.setenv("GTS_KERNEL", "team")
+    try:
+        dg = api.upload(g)
+        hs = api.upload_hw(hws)
+        B = hws.shape[0]
+        stride = api.scratch_bytes(dg, 2, flags) - api.scratch_bytes(dg, 1, flags)
+        scratch = torch.zeros(api.scratch_bytes(dg, B, flags), dtype=torch.uint8, device="cuda")
+        out = api.alloc_outputs(dg, B, flags)
+        api.simulate_hwset_into(dg, hs, 0, B, flags, *out, scratch)
+        torch.cuda.synchronize()
+        blk = scratch[:B * stride].view(B, stride)[:, stride - STATS_BYTES:].contiguous().view(torch.int64).cpu().numpy()
+    finally:
+        monkeypatch.delenv("GTS_KERNEL")
+    cyc, mk, st, dg_ = out
+    return (cyc.cpu().numpy().view(np.uint32) if cyc is not None else None, mk.cpu().numpy().view(np.uint32),
+            st.cpu().numpy(), dg_.cpu().numpy().view(np.uint64) if dg_ is not None else None), blk[:, 0], blk[:, 11]
+
+
+def check(torch, g, hws, flags, monkeypatch, what):
+    gpu, windows, waves = run_team_only(torch, g, hws, flags, monkeypatch)
+    st = gpu[2]
+    assert not np.any(st == STATUS_RETRY), f"{what}: handed back sims {np.flatnonzero(st == STATUS_RETRY)}"
+    ran = st != api.SIM_INFEASIBLE
+    assert np.all(windows[ran] > 0) and np.all(waves[ran] == -(-int(hws[:, 0].max()) // 64)), what
+    compare(g, hws, flags, gpu)
+    return int(ran.sum())
+
+
+@pytest.mark.parametrize("chunk", range(8))
+def test_team_random_graphs(torch_cuda, chunk, monkeypatch):
+    """200 random graphs (cross-CTA edges into shared nodes, fan-outs above
+    three, zero-work nodes) on machines of 1-256 SMs under all four flag
+    combinations."""
+    ran = 0
+    for seed in range(chunk * 25, chunk * 25 + 25):
+        rng = SplitMix64(seed, 89)
+        g = windowed_graph(rng)
+        assert window_eligible(g)
+        hws = windowed_machines(rng, rng.randint(1, 8))
+        flags = ALL | rng.choice([0, api.NO_CONTENTION, api.ORDER_AT_FINISH, api.NO_CONTENTION | api.ORDER_AT_FINISH])
+        note(f"team random seed={seed} N={g.n_nodes} E={g.n_edges} n_sm={hws[:, 0].tolist()} flags={flags}")
+        ran += check(torch_cuda, g, hws, flags, monkeypatch, f"seed {seed}")
+    assert ran > 0
+
+
+@pytest.mark.parametrize("name", ["gemm_512", "gemm_perwarp", "fa", "fa_causal", "decode_small", "decoder_tiny",
+                                  "simultaneous_loads"])
+def test_team_workloads(torch_cuda, name, monkeypatch):
+    """Each workload on machines whose SM counts sit at the edges of one to
+    four waves (the last also with more arrivals, and retirements, in one
+    cycle than a batch holds)."""
+    g = {
+        "gemm_512": lambda: W.gemm(512, 512, 512, 128, 128, 32, 2),
+        "gemm_perwarp": lambda: W.gemm(2048, 1024, 512, 64, 64, 32, 3, per_warp=True),
+        "fa": lambda: W.flash_attention(1, 4, 1024),
+        "fa_causal": lambda: W.flash_attention(1, 4, 1024, 128, 128, 64, causal=True),
+        "decode_small": lambda: W.splitkv_decode(batch=6, kv_min=64, kv_max=4096, seed=9),
+        "decoder_tiny": lambda: W.decoder_layer(tokens=256, hidden=512, heads=8, kv_heads=2, ffn=1024, d=64),
+        "simultaneous_loads": _simultaneous_loads_graph,
+    }[name]()
+    for sms in ((1, 3, 64), (65, 100, 128), (129, 132, 192), (193, 255, 256)):
+        hws = np.stack([H.preset("H100", n_sm=s, max_cta_per_sm=c, tensor_permille=t)
+                        for s in sms for c, t in ((32, 1000), (2, 2500))])
+        note(f"team {name} N={g.n_nodes} n_sm={sms}")
+        check(torch_cuda, g, hws, ALL, monkeypatch, f"{name} {sms}")
+
+
+def test_team_subpartitions(torch_cuda, monkeypatch):
+    """One server word per class, and (with a record of eight subpartitions in
+    the batch) one per subpartition lane."""
+    g = W.gemm(1024, 512, 512, 128, 128, 32, 3)
+    hws = H.sample_h100_sweep(78, 9)
+    hws[:, H.FIELDS["n_subpart"]] = [1, 2, 3, 4] * 2 + [4]
+    check(torch_cuda, g, hws, ALL, monkeypatch, "one word")
+    hws[4, H.FIELDS["n_subpart"]] = 8
+    check(torch_cuda, g, hws, ALL, monkeypatch, "one per lane")
+
+
+def test_team_hands_back_overflow(torch_cuda, monkeypatch):
+    """300 loads ready at once on one SM of a 256-SM machine fit no list: the
+    team kernel hands the simulation back, and the normal path finishes it."""
+    g = _wide_roots_graph()
+    hws = np.stack([H.preset("H100", n_sm=256, max_cta_per_sm=2), H.preset("H100", n_sm=1, max_cta_per_sm=2)])
+    gpu, _, _ = run_team_only(torch_cuda, g, hws, ALL, monkeypatch)
+    assert gpu[2][1] == STATUS_RETRY
+    res = api.simulate(api.upload(g), hws, ALL)
+    torch_cuda.cuda.synchronize()
+    compare(g, hws, ALL, api.to_numpy(res))
