@@ -61,7 +61,7 @@ struct NodeDev {                // 32 B, one per node and a sentinel after the l
   uint16_t sindeg[kInlineSucc]; // and their in-degrees
   uint16_t pad;                 // template records: kRecSink on the retiring sink
 };
-// Template record flag: the CTA's retiring sink (its kernel has pad[0] = 1:
+// Template record flag: the CTA's retiring sink (its kernel has sink_ret = 1:
 // every node reaches this load / store over DATA / SYNC edges, so the CTA
 // retires at its finish).
 constexpr uint16_t kRecSink = 1;
@@ -91,9 +91,29 @@ struct KernelDev {              // 48 B, one per kernel
   uint32_t t_base;              // first template record (and in-degree) of the kernel
   uint32_t t_ops;               // tops offset (low 16) | slots per class (high 16)
   uint32_t cluster;             // CTAs per cluster | kKernelRemote
-  uint32_t pad[3];              // pad[0]: 1 if the template's CTAs retire with their sink
+  uint32_t sink_ret;            // 1 if the template's CTAs retire with their sink
+  uint32_t t_slots;             // state slots per CTA of the compact template records, 0: none
+  uint32_t pad;
 };
 constexpr uint32_t kKernelRemote = 0x10000u;  // the kernel has REMOTE nodes
+// Compact template records (the team kernel's): eight words per node, one per
+// successor -- local node (bits 0-11), state slot (12-21), in-degree (22-26),
+// released at issue (27).  A compute node's successors fill words 0-7; a
+// memory node's are released at issue (words 0-3) or at completion (4-7).
+// Bits 28-31 hold the node's own fields: op slot (words 0, 1: four and three
+// bits), kRecSink (word 1, bit 31), the successors of words 0-7 / 0-3 (word
+// 2), whether it is a memory node (word 3, bit 28) and the successors of
+// words 4-7 (29-31).  A node of two or more in-edges counts its releases in a
+// state slot of its CTA.  Two nodes may share a slot when one of them is an
+// ancestor of (or is) every predecessor of the other: it is then ready, and
+// its slot back at zero, before the other's first release.  Two more slots:
+// one that stays at zero, for nodes of one in-edge, and one for the words
+// without a successor, whose in-degree of 0 no count reaches.  A template
+// that does not fit this (more nodes, slots, in-edges or successors, a node
+// that is a load in one CTA and a compute node in another, CTAs that do not
+// retire with their sink) has no compact records.
+constexpr uint32_t kCompactWords = 8;
+constexpr uint32_t kCompactMaxNodes = 4096, kCompactMaxSlots = 1024, kCompactMaxIndeg = 31;
 constexpr uint32_t kMaxTops = 128;   // class x slot op entries per graph (held in LDS)
 
 // Device-side view passed to kernels by value.
@@ -108,6 +128,7 @@ struct Image {
   const NodeDev* tnodes;        // template records (succ: local index | bits)
   const uint32_t* tsucc;        // template successors beyond the records' inline ones
   const uint16_t* tindeg;       // in-degree per template record
+  const uint32_t* crec;         // compact template records, parallel to tnodes
   const uint8_t* cclass;        // class of each CTA of a templated kernel
   const uint16_t* tops;         // [n_tops] class x slot -> op id
   const uint32_t* tile;         // [N] tile of each load / store, numbered 0..n_tiles-1 (kGraphTiles), else null
@@ -201,6 +222,9 @@ struct Launch {
   uint32_t clocks;             // windowed kernel: time its phases with the shader clock
   uint32_t team_ring;          // team kernel: memory arrivals per SM held in LDS
   uint32_t team_ret;           // team kernel: pending retirements held in LDS
+  uint32_t team_rec;           // team kernel: compact template records held in LDS
+  uint32_t team_own;           // team kernel: most resident CTAs of a kernel with compact records ...
+  uint32_t team_st;            // ... and state slots for them
   uint32_t srv_one;            // one server word per compute class (every compute op holds every subpartition
                                // lane of every record, so their lanes' times stay equal)
 };
@@ -276,30 +300,38 @@ __host__ __device__ inline WinLds win_lds(uint32_t P, uint32_t NS, uint32_t SS, 
 // launch, arrays per SM strided by the workgroup's TH threads.
 constexpr uint32_t kTeamCap = 256;    // memory arrivals (or retirements) per window
 constexpr uint32_t kTeamHeads = 6;    // of one SM's arrivals (the window is cut where more may be due)
-constexpr uint32_t kTeamKey = 0;      // batch keys, and eight past the end
-constexpr uint32_t kTeamOp = kTeamKey + 2u * (kTeamCap + 8u);
+constexpr uint32_t kTeamPad = 16;     // keys past the end of a batch
+constexpr uint32_t kTeamKey = 0;      // batch keys (u64), then their 32-bit order keys
+constexpr uint32_t kTeamKey32 = kTeamKey + 2u * (kTeamCap + kTeamPad);
+constexpr uint32_t kTeamOp = kTeamKey32 + kTeamCap + kTeamPad;
 constexpr uint32_t kTeamMend = kTeamOp + kTeamCap;
 constexpr uint32_t kTeamSorted = kTeamMend + kTeamCap;           // four words per arrival
 constexpr uint32_t kTeamExch = kTeamSorted + 4u * kTeamCap;      // two halves of four words per wave
 // dispatch state: next CTA, retired CTAs, current kernel, its first and end
 // CTA, the kernel whose start cycle is known, that cycle (words 0-6), CTA
 // slots per SM (u64, words 8-9), the running kernel, the window end after
-// the retirement phase, whether some thread gave up (words 10-12)
+// the retirement phase, whether some thread gave up, free CTA places, the
+// record's launch latencies (words 10-15)
 constexpr uint32_t kTeamCtl = kTeamExch + 32u;
-constexpr uint32_t kTeamNextCta = kTeamCtl;
+constexpr uint32_t kTeamNextCta = kTeamCtl, kTeamFree = kTeamCtl + 13u;
 constexpr uint32_t kTeamRed = kTeamCtl + 16u;      // two windows' words {earliest ready or arrival, retirement}
 constexpr uint32_t kTeamRetCnt = kTeamRed + 4u, kTeamRetMin = kTeamRetCnt + 1u;
 constexpr uint32_t kTeamFixedInit = kTeamRetMin + 1u - kTeamCtl;
-constexpr uint32_t kTeamFixed = (kTeamRetMin + 1u + 3u) & ~3u;
-static_assert(kTeamSorted % 4 == 0 && kTeamExch % 4 == 0 && kTeamCtl % 2 == 0 && kTeamFixedInit <= 64, "alignment");
+constexpr uint32_t kTeamSpare = (kTeamRetMin + 1u + 3u) & ~3u;  // four words for writes of lanes with nothing to write
+constexpr uint32_t kTeamFixed = kTeamSpare + 4u;
+constexpr uint32_t kTeamLog = 128;    // finished nodes per wave waiting for their outputs (three words each)
+static_assert(kTeamKey32 % 4 == 0 && kTeamSorted % 4 == 0 && kTeamExch % 4 == 0 && kTeamCtl % 2 == 0 &&
+                  kTeamFixedInit <= 64 && kTeamFixed % 4 == 0,
+              "alignment");
 struct TeamLds {
-  uint32_t optab, q, ret, srv, q_cnt, q_min, res, ring;
+  uint32_t optab, rec, q, ret, st, own, srv, q_cnt, q_min, res, log, ring;
   uint32_t total;
 };
 // TH: threads; P: op table entries (ops, then template class x slot entries);
 // SS: server words per SM; QP, RL, RT: ready entries and memory arrivals per
-// SM, and pending retirements held in LDS.
-__host__ __device__ inline TeamLds team_lds(uint32_t TH, uint32_t P, uint32_t SS, uint32_t QP, uint32_t RL, uint32_t RT) {
+// SM, and pending retirements held in LDS; REC, OWN, ST: as in Launch.
+__host__ __device__ inline TeamLds team_lds(uint32_t TH, uint32_t P, uint32_t SS, uint32_t QP, uint32_t RL, uint32_t RT,
+                                            uint32_t REC, uint32_t OWN, uint32_t ST) {
   TeamLds L;
   uint32_t o = kTeamFixed;
   auto take = [&o](uint32_t words) {
@@ -308,13 +340,20 @@ __host__ __device__ inline TeamLds team_lds(uint32_t TH, uint32_t P, uint32_t SS
     return r;
   };
   L.optab = take(4u * P);
+  L.rec = take(kCompactWords * REC);
   L.q = take(2u * QP * TH);
   L.ret = take(2u * RT);
-  L.srv = take(SS * TH);
+  L.st = take(ST);
+  L.own = take(2u * OWN);  // each place's class, and the free places
+  // kernels that run from LDS: a word for SYNC nodes, and up to four words
+  // are read from any server's on
+  L.srv = take((SS + (REC ? 4u : 0u)) * TH);
   L.q_cnt = take(TH);
   L.q_min = take(TH);
   L.res = take(TH);
-  L.ring = take(3u * RL * TH);
+  L.log = take(REC ? 3u * kTeamLog * (TH / 64u) : 0u);
+  o = (o + 3u) & ~3u;
+  L.ring = take(4u * RL * TH);
   L.total = o;
   return L;
 }

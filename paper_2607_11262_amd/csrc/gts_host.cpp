@@ -10,8 +10,8 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <unordered_map>
 #include <new>
+#include <unordered_map>
 #include <string>
 #include <vector>
 
@@ -24,6 +24,13 @@ hipError_t launch_window(const Launch& L, uint32_t lds_bytes, hipStream_t stream
 hipError_t launch_team(const Launch& L, uint32_t lds_bytes, hipStream_t stream);
 }
 
+// Kernels with compact template records of one shape: records, state slots per
+// CTA, the most CTAs of one of them, nodes of all of them.
+struct CompactShape {
+  uint32_t rec, slots, ctas;
+  uint64_t nodes;
+};
+
 struct gts_graph {
   gts::Image img;
   uint64_t bytes;
@@ -31,6 +38,9 @@ struct gts_graph {
   uint64_t max_tile_lines;
   bool all_mem_txn;  // every load / store streams at least one line (transaction-level memory)
   uint32_t full_lanes;  // bit n: at n_subpart = n every compute op holds every subpartition lane
+  // the kernels with compact template records, those of one shape together,
+  // the most nodes first
+  std::vector<CompactShape> compact;
 };
 
 struct gts_hwset {
@@ -58,6 +68,9 @@ bool is_compute(uint8_t c) { return c <= gts::C_SFU; }
 uint32_t cluster_of(const gts_graph_host* h, uint32_t k) { return h->kernel_cluster ? h->kernel_cluster[k] : 1u; }
 bool is_memory(uint8_t c) { return c == gts::C_GLOAD || c == gts::C_GSTORE; }
 
+constexpr uint32_t kMostOwners = 2048;  // most CTAs of a simulation with their state in LDS
+constexpr size_t kMostShapes = 64;
+
 // A kernel whose CTAs share one template of node records.
 struct KTemplate {
   uint32_t t_n = 0;     // nodes per CTA (0: not templated)
@@ -66,6 +79,7 @@ struct KTemplate {
   uint32_t nslot = 0;
   uint32_t tsucc = 0;   // first template successor
   int32_t sink = -1;    // local index of the template's retiring sink, or -1
+  uint32_t slots = 0;   // state slots per CTA of its compact records, 0: it has none
 };
 
 // Everything the image needs that is derived from a valid host graph.
@@ -78,6 +92,7 @@ struct Derived {
   std::vector<uint16_t> tslot;   // per template record: slot
   std::vector<uint16_t> tops;    // class x slot -> op
   uint32_t n_tnodes = 0, n_tsucc = 0;
+  std::vector<uint32_t> crec;         // compact template records
   uint32_t n_tiles = 0;          // distinct tiles named by loads / stores
   uint64_t max_tile_lines = 0;   // the most lines of any of them
   bool all_mem_txn = false;      // every load / store streams at least one line (transaction-level memory)
@@ -94,12 +109,15 @@ struct Derived {
 // Kernels that would take the class x slot table past kMaxTops entries, or
 // that have more than 255 classes, stay expanded.  GTS_TEMPLATES=0 turns the
 // detection off.
+void compact_template(const gts_graph_host* h, Derived* d, uint32_t u0, KTemplate& t);
+
 void find_templates(const gts_graph_host* h, Derived* d) {
   const uint32_t K = h->n_kernels, C = h->n_ctas;
   d->ktmpl.assign(K, KTemplate());
   d->cclass.assign(C, 0);
   d->tslot.clear();
   d->tops.clear();
+  d->crec.clear();
   d->n_tnodes = d->n_tsucc = 0;
   if (const char* e = std::getenv("GTS_TEMPLATES"))
     if (std::strcmp(e, "0") == 0) return;
@@ -209,6 +227,89 @@ void find_templates(const gts_graph_host* h, Derived* d) {
     }
     d->n_tnodes += n;
     d->n_tsucc += h->succ_ptr[nb[c0] + n] - h->succ_ptr[nb[c0]];
+    d->crec.resize((size_t)d->n_tnodes * gts::kCompactWords, 0);
+    compact_template(h, d, nb[c0], t);
+  }
+}
+
+// Compact records of a template (gts_dev.h), if it fits them: state slots for
+// its nodes of two or more in-edges, each node into the first slot whose last
+// node is an ancestor of, or is, every predecessor of it.
+void compact_template(const gts_graph_host* h, Derived* d, uint32_t u0, KTemplate& t) {
+  const uint32_t n = t.t_n;
+  if (n > gts::kCompactMaxNodes || t.sink < 0) return;
+  auto deg = [&](uint32_t i) { return h->succ_ptr[u0 + i + 1] - h->succ_ptr[u0 + i]; };
+  auto edge = [&](uint32_t i, uint32_t j) { return h->succ[h->succ_ptr[u0 + i] + j]; };
+  auto at_issue = [&](uint32_t i, uint32_t j) { return (edge(i, j) >> GTS_EDGE_KIND_SHIFT) == GTS_EDGE_ORDER; };
+  std::vector<std::vector<uint32_t>> pred(n);
+  std::vector<uint8_t> mem(n);
+  const uint32_t nclass = ((uint32_t)d->tops.size() - t.t_ops) / t.nslot;
+  for (uint32_t i = 0; i < n; ++i) {
+    const uint16_t* op = &d->tops[t.t_ops + d->tslot[t.t_base + i]];
+    mem[i] = is_memory(h->op_cls[op[0]]);
+    for (uint32_t q = 1; q < nclass; ++q)
+      if ((bool)is_memory(h->op_cls[op[q * t.nslot]]) != (bool)mem[i]) return;
+    uint32_t issue = 0;
+    for (uint32_t j = 0; j < deg(i); ++j) {
+      pred[(edge(i, j) & GTS_EDGE_TARGET_MASK) - u0].push_back(i);
+      issue += at_issue(i, j);
+    }
+    if (mem[i] ? issue > 4u || deg(i) - issue > 4u : deg(i) > 8u) return;
+  }
+  // topological order, with each node's ancestors
+  const uint32_t words = (n + 63) / 64;
+  std::vector<uint64_t> anc((size_t)n * words, 0);
+  std::vector<uint32_t> order, left(n);
+  order.reserve(n);
+  for (uint32_t i = 0; i < n; ++i) {
+    if (pred[i].size() > gts::kCompactMaxIndeg) return;
+    left[i] = (uint32_t)pred[i].size();
+    if (!left[i]) order.push_back(i);
+  }
+  for (uint32_t q = 0; q < order.size(); ++q) {
+    const uint32_t i = order[q];
+    uint64_t* a = &anc[(size_t)i * words];
+    for (uint32_t p : pred[i]) {
+      const uint64_t* b = &anc[(size_t)p * words];
+      for (uint32_t w = 0; w < words; ++w) a[w] |= b[w];
+      a[p / 64] |= 1ull << (p % 64);
+    }
+    for (uint32_t j = 0; j < deg(i); ++j) {
+      const uint32_t v = (edge(i, j) & GTS_EDGE_TARGET_MASK) - u0;
+      if (--left[v] == 0) order.push_back(v);
+    }
+  }
+  std::vector<uint32_t> slot(n, 0), last;  // last: the latest node of each slot
+  for (uint32_t i : order) {
+    if (pred[i].size() < 2) continue;
+    uint32_t s = 0;
+    for (; s < last.size(); ++s) {
+      const uint32_t a = last[s];
+      bool ok = true;
+      for (uint32_t p : pred[i]) ok = ok && (p == a || ((anc[(size_t)p * words + a / 64] >> (a % 64)) & 1u));
+      if (ok) break;
+    }
+    if (s == last.size()) last.push_back(0);
+    last[s] = i;
+    slot[i] = s;
+  }
+  const uint32_t zero = (uint32_t)last.size(), none = zero + 1u;
+  if (none + 1u > gts::kCompactMaxSlots) return;
+  t.slots = none + 1u;
+  for (uint32_t i = 0; i < n; ++i) {
+    uint32_t* r = &d->crec[(size_t)(t.t_base + i) * gts::kCompactWords];
+    for (uint32_t w = 0; w < gts::kCompactWords; ++w) r[w] = none << 12;
+    uint32_t first = 0, second = 0;
+    for (uint32_t j = 0; j < deg(i); ++j) {
+      const uint32_t v = (edge(i, j) & GTS_EDGE_TARGET_MASK) - u0, in = (uint32_t)pred[v].size();
+      const uint32_t w = mem[i] && !at_issue(i, j) ? 4u + second++ : first++;
+      r[w] = v | (in > 1u ? slot[v] : zero) << 12 | in << 22 | (at_issue(i, j) ? 1u << 27 : 0u);
+    }
+    const uint32_t op = d->tslot[t.t_base + i];
+    r[0] |= (op & 15u) << 28;
+    r[1] |= (op >> 4) << 28 | (t.sink == (int32_t)i ? (uint32_t)gts::kRecSink << 31 : 0u);
+    r[2] |= first << 28;
+    r[3] |= (mem[i] ? 1u << 28 : 0u) | second << 29;
   }
 }
 
@@ -484,7 +585,7 @@ int check_graph(const gts_graph_host* h, Derived* d) {
 }
 
 struct ImageLayout {
-  uint64_t ops, nodes, succ, ctas, kernels, roots, indeg, tnodes, tsucc, tindeg, cclass, tops, tile, txn_ptr, txn_line,
+  uint64_t ops, nodes, succ, ctas, kernels, roots, indeg, tnodes, tsucc, tindeg, crec, cclass, tops, tile, txn_ptr, txn_line,
       total;
 };
 
@@ -512,6 +613,8 @@ ImageLayout image_layout(const gts_graph_host* h, const Derived& d) {
   off = align_up(off + (uint64_t)d.n_tsucc * 4, gts::kAlign);
   L.tindeg = off;
   off = align_up(off + (uint64_t)d.n_tnodes * 2, gts::kAlign);
+  L.crec = off;
+  off = align_up(off + (uint64_t)d.crec.size() * 4, gts::kAlign);
   L.cclass = off;
   off = align_up(off + (uint64_t)h->n_ctas, gts::kAlign);
   L.tops = off;
@@ -672,14 +775,18 @@ uint32_t device_cus() {
 }
 
 // The team kernel (one workgroup per simulation, a wave per 64 SMs) takes the
-// batch: it shortens a simulation's chain at the price of more work, which
-// pays while wave slots are idle.  Measured, windowed / team: split-KV decode
-// (130,576 nodes) x 1024 records 93.3 / 49.9 ms, flash attention (659,456) x
-// 256 198 / 113 ms; at 4096 records a 24,832-node GEMM 11.1 / 10.6 ms and a
-// 401,408-node one 229 / 268 ms.
-bool team_batch(uint32_t mode, uint32_t B) {
+// batch: it shortens a simulation's chain at the price of more wave
+// instructions, which pays while wave slots are idle, and on machines of at
+// most 64 SMs, where it has one wave too, at any size.  Measured, windowed /
+// team: split-KV decode (130,576 nodes) x 1024 records 91 / 39 ms, flash
+// attention (659,456) x 256 203 / 80 ms; 4096 records of 1, 16, 48 and 64 SMs:
+// 24,832-node GEMM 246 / 198, 23.6 / 18.4, 11.4 / 9.1 and 11.0 / 8.8 ms.
+// 4096 records of 64-192 SMs are faster too when nothing else runs (that GEMM
+// 10.2 / 8.4 ms), but the GEMM design sweep, whose launches overlap on two
+// streams, ran at 9.5e9 against 1.02e10 tile-nodes/s.
+bool team_batch(uint32_t mode, uint32_t B, uint32_t max_nsm) {
   constexpr uint32_t kTeamMost = 1024;
-  return mode == gts::kWinPlain && B <= kTeamMost;
+  return mode == gts::kWinPlain && (B <= kTeamMost || max_nsm <= 64u);
 }
 
 // LDS one workgroup may have on the current device (0 if it cannot be queried).
@@ -691,22 +798,61 @@ uint32_t device_lds() {
   return (uint32_t)n;
 }
 
-// LDS bytes of a team launch, its list sizes chosen for the workgroups a CU
-// will hold.
+// LDS bytes of a team launch.  The workgroups a CU will hold share its 160
+// KB; each first gets lists that the common step fits (eight entries beyond
+// its releases), then the compact template records, then the CTAs' state
+// slots, then longer lists.  What does not fit stays in global memory.
 uint32_t team_sizes(const gts_graph* g, gts::Launch& L, uint32_t wstride) {
   const uint32_t TH = 64u * ((L.max_nsm + 63u) / 64u), P = g->img.n_ops + g->img.n_tops;
   const uint32_t cus = device_cus();
-  const uint32_t per_cu = cus ? std::max(1u, (L.B + cus - 1u) / cus) : 1u;
+  // the registers allow twelve waves per CU
+  const uint32_t most = std::max(1u, 12u * 64u / TH);
+  const uint32_t per_cu = cus ? std::min(most, std::max(1u, (L.B + cus - 1u) / cus)) : 1u;
   const uint32_t budget = 160u * 1024u / per_cu;
-  uint32_t qp = 4, rl = 6, rt = 64;
-  auto bytes = [&](uint32_t q, uint32_t r, uint32_t t) { return 4u * gts::team_lds(TH, P, wstride, q, r, t).total; };
-  struct { uint32_t q, r, t; } const up[] = {{8, 6, 64}, {8, 8, 256}, {12, 12, 256}, {16, 16, 512}, {32, 16, 512}, {64, 32, 512}};
-  for (const auto& u : up)
-    if (bytes(u.q, u.r, u.t) <= budget) qp = u.q, rl = u.r, rt = u.t;
-  L.qp = qp;
-  L.team_ring = rl;
-  L.team_ret = rt;
-  return bytes(qp, rl, rt);
+  L.qp = 4;
+  L.team_ring = 4;
+  L.team_ret = 64;
+  L.team_rec = L.team_own = L.team_st = 0;
+  auto bytes = [&] {
+    return 4u * gts::team_lds(TH, P, wstride, L.qp, L.team_ring, L.team_ret, L.team_rec, L.team_own, L.team_st).total;
+  };
+  struct Lists { uint32_t q, r, t; };
+  auto lists = [&](const Lists& u, uint32_t limit) {
+    const gts::Launch old = L;
+    L.qp = std::max(L.qp, u.q), L.team_ring = std::max(L.team_ring, u.r), L.team_ret = std::max(L.team_ret, u.t);
+    if (bytes() > limit) L = old;
+  };
+  if (!g->compact.empty()) {
+    // lists that the common step fits, then the records of the shape with the
+    // most nodes that leaves room for its places, then places, then the
+    // records of smaller shapes come free
+    const gts::Launch old = L;
+    L.qp = 8;
+    L.team_rec = 1;
+    for (const Lists& u : {Lists{10, 4, 64}, Lists{12, 6, 64}, Lists{16, 6, 128}}) lists(u, budget / 2u);
+    const uint32_t least = bytes();
+    uint32_t rec = 0, slots = 1, ctas = 1;
+    for (const CompactShape& s : g->compact) {
+      const uint64_t need = 4ull * gts::kCompactWords * s.rec;
+      if (least + need + 4ull * (s.slots + 2u) * std::min(s.ctas, L.max_nsm) > budget) continue;
+      if (!rec) {
+        rec = s.rec;
+        slots = s.slots;
+      }
+      if (s.rec <= rec) ctas = std::max(ctas, s.ctas), slots = std::max(slots, s.slots);
+    }
+    if (rec) {
+      L.team_rec = rec;
+      const uint32_t room = (budget - least - 4u * gts::kCompactWords * rec) / 4u;
+      L.team_own = std::min(std::min(kMostOwners, ctas), room / (slots + 2u));
+      L.team_st = L.team_own * slots;
+    } else {
+      L = old;
+    }
+  }
+  for (const Lists& u : {Lists{6, 4, 64}, Lists{8, 6, 64}, Lists{12, 6, 128}, Lists{16, 8, 256}, Lists{24, 12, 512}, Lists{32, 16, 1024}})
+    lists(u, budget);
+  return bytes();
 }
 
 int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_nsm, uint32_t max_nsub, uint32_t max_noc,
@@ -788,7 +934,7 @@ int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_
   const bool window_only = windowed && force && std::strcmp(force, "window") == 0;
   const bool team_only = windowed && force && std::strcmp(force, "team") == 0;
   hipError_t e = hipSuccess;
-  if (windowed && !window_only && (team_only || team_batch(mode, B))) {
+  if (windowed && !window_only && (team_only || team_batch(mode, B, max_nsm))) {
     gts::Launch T = L;
     const uint32_t lds_team = team_sizes(g, T, wstride);
     if (lds_team <= device_lds()) {
@@ -990,7 +1136,8 @@ int gts_graph_upload(const gts_graph_host* h, void* dev_image, uint64_t dev_byte
     ks[k].t_n = t.t_n;
     ks[k].t_base = t.t_base;
     ks[k].t_ops = t.t_ops | t.nslot << 16;
-    ks[k].pad[0] = t.sink >= 0 ? 1u : 0u;  // retires with its sink (kKernelSinkRetire)
+    ks[k].sink_ret = t.sink >= 0 ? 1u : 0u;
+    ks[k].t_slots = t.slots;
     bool remote = false;
     for (uint32_t v = h->cta_node_begin[ks[k].cta_begin]; v < h->cta_node_begin[ks[k].cta_end] && !remote; ++v)
       remote = h->op_cls[h->node_op[v]] == GTS_REMOTE;
@@ -1026,6 +1173,7 @@ int gts_graph_upload(const gts_graph_host* h, void* dev_image, uint64_t dev_byte
     }
   }
   std::memcpy(img.data() + L.cclass, d.cclass.data(), d.cclass.size());
+  if (!d.crec.empty()) std::memcpy(img.data() + L.crec, d.crec.data(), d.crec.size() * 4);
   if (d.n_tiles) {
     // tiles numbered densely in order of first appearance (the kernel indexes
     // its per-tile stamps by them)
@@ -1059,12 +1207,28 @@ int gts_graph_upload(const gts_graph_host* h, void* dev_image, uint64_t dev_byte
   g->img.tnodes = reinterpret_cast<const gts::NodeDev*>(base + L.tnodes);
   g->img.tsucc = reinterpret_cast<const uint32_t*>(base + L.tsucc);
   g->img.tindeg = reinterpret_cast<const uint16_t*>(base + L.tindeg);
+  g->img.crec = reinterpret_cast<const uint32_t*>(base + L.crec);
   g->img.cclass = reinterpret_cast<const uint8_t*>(base + L.cclass);
   g->img.tops = reinterpret_cast<const uint16_t*>(base + L.tops);
   g->img.n_tops = (uint32_t)d.tops.size();
   g->img.tile = d.n_tiles ? reinterpret_cast<const uint32_t*>(base + L.tile) : nullptr;
   g->img.n_tiles = d.n_tiles;
   g->max_tile_lines = d.max_tile_lines;
+  for (uint32_t k = 0; k < h->n_kernels; ++k) {
+    const KTemplate& t = d.ktmpl[k];
+    if (!t.slots) continue;
+    const uint32_t c = h->kernel_cta_begin[k + 1] - h->kernel_cta_begin[k];
+    auto it = std::find_if(g->compact.begin(), g->compact.end(),
+                           [&](const CompactShape& s) { return s.rec == t.t_n && s.slots == t.slots; });
+    if (it == g->compact.end()) {
+      if (g->compact.size() >= kMostShapes) continue;
+      it = g->compact.insert(it, CompactShape{t.t_n, t.slots, 0u, 0u});
+    }
+    it->ctas = std::max(it->ctas, c);
+    it->nodes += (uint64_t)c * t.t_n;
+  }
+  std::sort(g->compact.begin(), g->compact.end(),
+            [](const CompactShape& a, const CompactShape& b) { return a.nodes > b.nodes; });
   g->full_lanes = d.full_lanes;
   g->all_mem_txn = d.all_mem_txn;
   const bool txn = !d.txn_line.empty();

@@ -572,7 +572,7 @@ struct WSim {
     t_base = uni(kd.t_base);
     t_ops = uni(kd.t_ops & 0xFFFFu);
     t_nslot = uni(kd.t_ops >> 16);
-    sink_ret = uni(kd.pad[0]) != 0;
+    sink_ret = uni(kd.sink_ret) != 0;
   }
 
   // kernel k's record, read as words from global memory

@@ -49,7 +49,7 @@ def check(torch, g, hws, flags, monkeypatch, what):
     st = gpu[2]
     assert not np.any(st == STATUS_RETRY), f"{what}: handed back sims {np.flatnonzero(st == STATUS_RETRY)}"
     ran = st != api.SIM_INFEASIBLE
-    assert np.all(windows[ran] > 0) and np.all(waves[ran] == -(-int(hws[:, 0].max()) // 64)), what
+    assert np.all(windows[ran] > 0) and np.all(waves[ran] == -(-hws[ran, 0].astype(int) // 64)), what
     compare(g, hws, flags, gpu)
     return int(ran.sum())
 
@@ -91,6 +91,17 @@ def test_team_workloads(torch_cuda, name, monkeypatch):
                         for s in sms for c, t in ((32, 1000), (2, 2500))])
         note(f"team {name} N={g.n_nodes} n_sm={sms}")
         check(torch_cuda, g, hws, ALL, monkeypatch, f"{name} {sms}")
+
+
+def test_team_short_lists(torch_cuda, monkeypatch):
+    """A batch that fills every CU (each workgroup gets the shortest lists and
+    rings): more arrivals of one SM, pending retirements and ready nodes than
+    LDS holds, on kernels in LDS and in global memory."""
+    for g in (W.splitkv_decode(batch=3, kv_min=64, kv_max=4096, seed=9), W.gemm(512, 512, 512, 64, 64, 32, 4)):
+        hws = np.concatenate([np.stack([H.preset("H100", n_sm=s, max_cta_per_sm=c) for s, c in
+                                        ((192, 32), (40, 32), (7, 8), (1, 32))]), H.sample_h100_sweep(45, 1020)])
+        note(f"team short lists N={g.n_nodes} B={hws.shape[0]}")
+        check(torch_cuda, g, hws, ALL, monkeypatch, g.name)
 
 
 def test_team_subpartitions(torch_cuda, monkeypatch):
