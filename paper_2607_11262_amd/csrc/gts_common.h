@@ -1,5 +1,5 @@
 // gts_common.h — device helpers shared by the simulation kernels of
-// libgts.so (wave reductions, private-scratch accessors, duration table).
+// libgts.so (private-scratch accessors, duration table).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -20,24 +20,6 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint64_t uni64(uint64_t x) {
   return ((uint64_t)uni((uint32_t)(x >> 32)) << 32) | uni((uint32_t)x);
-}
-
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    uint64_t y = __shfl_xor(x, o, 64);
-    x = y < x ? y : x;
-  }
-  return x;
-}
-
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    uint64_t y = __shfl_xor(x, o, 64);
-    x = y > x ? y : x;
-  }
-  return x;
 }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t lane) {

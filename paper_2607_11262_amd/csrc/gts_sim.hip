@@ -6,8 +6,14 @@
 // over pending events, the release of a node's out-edges (one lane per
 // edge), the search for the SM with the most free slots, the scan of a
 // dispatched CTA's root nodes, and appending newly ready nodes (ballot +
-// prefix count).  Per-SM server state and the per-op duration table live in
-// LDS; per-node and per-CTA state live in the simulation's scratch slice.
+// prefix count).  What bounds it is the chain of an event: its record, then the
+// states of its successors, and the instructions around them.  Wave minima by
+// DPP instead of six dependent crossbar shuffles, and one pass over a node's
+// edges instead of one per kind of release, took a NoC study's 2048
+// simulations of a 14,592-node graph from 51.4 to 42.4 ms; the first 256
+// pending events in registers instead of scratch changed nothing.
+// Per-SM server state and the per-op duration table live in LDS; per-node and
+// per-CTA state live in the simulation's scratch slice.
 //
 // Timing rules (GTSim Sec. 5.1-5.3, readings fixed where the paper is
 // silent; the CPU oracle states the same rules independently):
@@ -53,9 +59,12 @@
 //    its largest finish_j, when its last transaction arrives.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+
 #include "../../include/gts.h"
 #include "gts_dev.h"
 #include "gts_common.h"
+#include "gts_wave.h"
 
 namespace gts {
 
@@ -110,10 +119,13 @@ struct Sim {
     npend += (uint32_t)__popcll(m);
   }
 
-  // Release the out-edges of a node selected by `which`: 0 = ORDER edges
-  // released at issue, 1 = every other edge, released at completion.
+  // Release the out-edges of a node selected by `which` (bit 0: the ORDER
+  // edges released at issue, at s1; bit 1: every other edge, released at
+  // completion, at f).  One pass over the edges takes both: their states are
+  // read together, not one round trip per kind.
+  static constexpr uint32_t kAtIssue = 1u, kAtEnd = 2u;
   static_assert(kInlineSucc == 3, "release reads the record's three inline successor copies");
-  __device__ void release(uint32_t v, const NodeDev& rec, uint32_t which, uint64_t r, uint32_t src_cta,
+  __device__ void release(uint32_t v, const NodeDev& rec, uint32_t which, uint64_t s1, uint64_t f, uint32_t src_cta,
                           uint32_t src_sm) {
     const bool ofin = (flags & GTS_ORDER_AT_FINISH) != 0;
     const uint32_t deg = rec.op_nsucc >> 16;
@@ -128,7 +140,8 @@ struct Sim {
       const uint32_t kind = ent >> GTS_EDGE_KIND_SHIFT;
       const uint32_t w = ent & GTS_EDGE_TARGET_MASK;
       const bool at_issue = (kind & kDevOrder) && !ofin;
-      const bool sel = active && (at_issue == (which == 0));
+      const bool sel = active && (which & (at_issue ? kAtIssue : kAtEnd)) != 0u;
+      const uint64_t r = at_issue ? s1 : f;
       bool ready = false;
       uint64_t key = 0;
       uint32_t aux = 0;
@@ -159,12 +172,18 @@ struct Sim {
     }
   }
 
-  // Record (start, finish) of node v; CTA bookkeeping; false on overflow.
-  __device__ bool complete(uint32_t v, const NodeDev& rec, uint64_t s, uint64_t f, uint32_t sm) {
+  // Node v runs from s to f: its edges of `which` are released, its cycles
+  // recorded, its CTA's count and largest finish updated.  The CTA's words are
+  // read before the edges' states are, and everything is stored after both
+  // (loads and stores return in order: a load behind a store waits for it).
+  __device__ void finish(uint32_t v, const NodeDev& rec, uint64_t s, uint64_t f, uint32_t sm, uint32_t which) {
     if (f > kMaxCycle) {
       overflow = 1;
-      return false;
+      return;
     }
+    const uint32_t c = rec.cta;
+    const uint64_t lm = pld(reinterpret_cast<const uint64_t*>(&cst[c].left));  // left | maxfin << 32
+    release(v, rec, which, s + 1, f, c, sm);
     if (out_cycles && lane == 0) {
       uint64_t* o = reinterpret_cast<uint64_t*>(out_cycles) + ((uint64_t)b * G.n_nodes + v);
       *o = ((uint64_t)(uint32_t)f << 32) | (uint32_t)s;
@@ -172,19 +191,14 @@ struct Sim {
     digest += mix64(((s << 32) | f) ^ mix64((uint64_t)v + 1));
     makespan = (uint32_t)f > makespan ? (uint32_t)f : makespan;
     ++nfin;
-    const uint32_t c = rec.cta;
-    uint32_t left = pld(&cst[c].left) - 1;
-    uint32_t mf = pld(&cst[c].maxfin);
+    const uint32_t left = uni((uint32_t)lm) - 1u;
+    uint32_t mf = uni((uint32_t)(lm >> 32));
     mf = (uint32_t)f > mf ? (uint32_t)f : mf;
-    left = uni(left);
-    mf = uni(mf);
-    if (lane == 0) {
-      pst(&cst[c].left, left);
-      pst(&cst[c].maxfin, mf);
-    }
+    if (lane == 0) pst(reinterpret_cast<uint64_t*>(&cst[c].left), ((uint64_t)mf << 32) | left);
     if (left == 0) push_one(mkkey(mf, kEvRetire, c), sm);
-    return true;
   }
+  static_assert(offsetof(CtaState, left) % 8 == 0 && offsetof(CtaState, maxfin) == offsetof(CtaState, left) + 4,
+                "left and maxfin are one aligned 64-bit word");
 
   // Node of rank r in placement slot j of a NoC domain, or -1 when the
   // placement list has no slot j: strips of consecutive nodes, on a mesh
@@ -291,7 +305,7 @@ struct Sim {
         const uint64_t k = (fr << 32) | (0xFFFFFFFFu - m);
         best = k > best ? k : best;
       }
-      best = uni64(wave_max_u64(best));
+      best = uni64(wmax64(best));
       if ((best >> 32) == 0) return;  // every SM is full
       const uint32_t sm = 0xFFFFFFFFu - (uint32_t)best;
       if (!kstart_valid || kstart_k != cur_k) {
@@ -328,32 +342,25 @@ struct Sim {
     if (cls <= C_SFU) {
       const uint32_t lanes = (od.w >> 8) & 0xFFu;
       S += od.w >> 16;  // this class's lanes
-      uint32_t a = 0;
-      if (!nocont && lane < nsub && ((lanes >> lane) & 1u)) a = S[lane];
       uint64_t s = (uint64_t)t;
       if (!nocont) {
-        uint64_t m = wave_max_u64(a);
-        m = uni64(m);
+        uint32_t a = 0;
+        if (lane < nsub && ((lanes >> lane) & 1u)) a = S[lane];
+        const uint32_t m = nsub == 1u ? uni(a) : wave_max_u32(a);
         s = m > s ? m : s;
       }
       const uint64_t f = s + od.x + od.z;
-      if (!complete(v, rec, s, f, sm)) return;
-      if (lane < nsub && ((lanes >> lane) & 1u)) S[lane] = (uint32_t)(s + od.x);
-      release(v, rec, 0, s + 1, rec.cta, sm);
-      release(v, rec, 1, f, rec.cta, sm);
+      if (f <= kMaxCycle && lane < nsub && ((lanes >> lane) & 1u)) S[lane] = (uint32_t)(s + od.x);
+      finish(v, rec, s, f, sm, kAtIssue | kAtEnd);
     } else if (cls == C_SMEM) {
       const uint32_t a = S[smem_w];
       const uint64_t s = nocont ? (uint64_t)t : (a > t ? a : t);
       const uint64_t f = s + od.x + od.z;
-      if (!complete(v, rec, s, f, sm)) return;
-      if (lane == 0) S[smem_w] = (uint32_t)(s + od.x);
-      release(v, rec, 0, s + 1, rec.cta, sm);
-      release(v, rec, 1, f, rec.cta, sm);
+      if (f <= kMaxCycle && lane == 0) S[smem_w] = (uint32_t)(s + od.x);
+      finish(v, rec, s, f, sm, kAtIssue | kAtEnd);
     } else if (cls == C_SYNC) {
       const uint64_t f = (uint64_t)t + od.z;
-      if (!complete(v, rec, t, f, sm)) return;
-      release(v, rec, 0, (uint64_t)t + 1, rec.cta, sm);
-      release(v, rec, 1, f, rec.cta, sm);
+      finish(v, rec, t, f, sm, kAtIssue | kAtEnd);
     } else if (cls == C_REMOTE) {
       // the target CTA (same cluster) and the route between the two SMs'
       // nodes of their NoC domain; lane i holds route server i
@@ -385,14 +392,12 @@ struct Sim {
       uint64_t s = (uint64_t)t;
       if (!nocont) {
         const uint32_t av = lane < nr ? dav[idx] : 0u;
-        uint64_t m = uni64(wave_max_u64(av));
+        const uint32_t m = wave_max_u32(av);
         s = m > s ? m : s;
       }
       const uint64_t f = s + od.x + lat;
-      if (!complete(v, rec, s, f, sm)) return;
-      if (lane < nr) dav[idx] = (uint32_t)(s + od.x);
-      release(v, rec, 0, s + 1, rec.cta, sm);
-      release(v, rec, 1, f, rec.cta, sm);
+      if (f <= kMaxCycle && lane < nr) dav[idx] = (uint32_t)(s + od.x);
+      finish(v, rec, s, f, sm, kAtIssue | kAtEnd);
     } else {
       const uint32_t a = S[smem_w + 1];
       const uint64_t s = nocont ? (uint64_t)t : (a > t ? a : t);
@@ -408,7 +413,7 @@ struct Sim {
       // the node's state word is free once it issues: an addressed node keeps
       // its start (high) and the largest finish of its transactions so far
       if (n && lane == 0) pst(&state[v], s << 32);
-      release(v, rec, 0, s + 1, rec.cta, sm);
+      release(v, rec, kAtIssue, s + 1, 0, rec.cta, sm);
       push_one(mkkey(s, kEvMem, v), sm);  // transaction 0 (aux: SM | transaction << 10)
     }
   }
@@ -447,8 +452,7 @@ struct Sim {
       push_one(mkkey(s + cdiv64((uint64_t)(j + 1) * GTS_LINE_BYTES * 65536ull, rg), kEvMem, v), sm | (j + 1) << 10);
       return;
     }
-    if (!complete(v, rec, s, f, sm)) return;
-    release(v, rec, 1, f, rec.cta, sm);
+    finish(v, rec, s, f, sm, kAtEnd);
   }
 
   // Inclusive prefix sum across the wave.
@@ -523,8 +527,7 @@ struct Sim {
       l2_av = mend << 16;
     const uint64_t e = (uint64_t)t + od.x;
     const uint64_t f = (e > mend ? e : mend) + lat;
-    if (!complete(v, rec, t, f, sm)) return;
-    release(v, rec, 1, f, rec.cta, sm);
+    finish(v, rec, t, f, sm, kAtEnd);
   }
 };
 
@@ -661,10 +664,10 @@ extern "C" __global__ __launch_bounds__(64) void gts_sim_wave(Launch L) {
           ba = a[j];
         }
     }
-    const uint64_t mn = uni64(wave_min_u64(best));
+    const uint64_t mn = uni64(wmin64(best));
     const uint64_t who = __ballot(best == mn);
-    const uint32_t src = (uint32_t)__ffsll((unsigned long long)who) - 1u;
-    const uint32_t idx = (uint32_t)__shfl(bi, src, 64);
+    const int src = __ffsll((unsigned long long)who) - 1;
+    const uint32_t idx = lane_u32(bi, src);
     const uint32_t t = (uint32_t)(mn >> 32);
     const uint32_t kind = (uint32_t)(mn >> 30) & 3u;
     const uint32_t id = (uint32_t)mn & GTS_EDGE_TARGET_MASK;
@@ -673,7 +676,7 @@ extern "C" __global__ __launch_bounds__(64) void gts_sim_wave(Launch L) {
       dispatch_due = false;
       continue;
     }
-    const uint32_t aux = uni((uint32_t)__shfl(ba, src, 64));
+    const uint32_t aux = lane_u32(ba, src);
     if (idx != last && lane == 0) {
       pst(&S.pkey[idx], lk);
       pst(&S.paux[idx], la);

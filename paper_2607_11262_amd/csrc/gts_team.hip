@@ -127,19 +127,6 @@ __device__ __forceinline__ MP wave_incl_mp(MP c) {
   c = after(dpp_mp<kRowBcast31, 0xC>(c), c);
   return c;
 }
-// Wave-wide max of a u32 (uniform result).
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
-  auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
-  x = mx(x, dpp<kRowShr1>(0u, x));
-  x = mx(x, dpp<kRowShr2>(0u, x));
-  x = mx(x, dpp<kRowShr4>(0u, x));
-  x = mx(x, dpp<kRowShr8>(0u, x));
-  x = mx(x, dpp<kRowBcast15, 0xA>(0u, x));
-  x = mx(x, dpp<kRowBcast31, 0xC>(0u, x));
-  return lane_u32(x, 63);
-}
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) { return ~wave_max_u32(~x); }
-
 // Barrier that orders LDS only: global memory is private to a thread's SM,
 // atomic, or handed over at a full barrier.
 template <uint32_t NW>

@@ -1,4 +1,4 @@
-// gts_wave.h — wave-level helpers shared by the windowed kernels: cross-lane
+// gts_wave.h — wave-level helpers shared by the simulation kernels: cross-lane
 // sums, minima and max-plus scans by DPP, global-memory pointer types, and
 // the node record held in registers.
 #pragma once
@@ -89,6 +89,19 @@ __device__ __forceinline__ uint64_t wave_ext_u64(uint64_t x) {
   }
   return r;
 }
+// Wave-wide max of a u32 (uniform result).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+  x = mx(x, dpp<kRowShr1>(0u, x));
+  x = mx(x, dpp<kRowShr2>(0u, x));
+  x = mx(x, dpp<kRowShr4>(0u, x));
+  x = mx(x, dpp<kRowShr8>(0u, x));
+  x = mx(x, dpp<kRowBcast15, 0xA>(0u, x));
+  x = mx(x, dpp<kRowBcast31, 0xC>(0u, x));
+  return lane_u32(x, 63);
+}
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) { return ~wave_max_u32(~x); }
+
 __device__ __forceinline__ uint64_t wmin64(uint64_t x) { return wave_ext_u64<false>(x); }
 __device__ __forceinline__ uint64_t wmax64(uint64_t x) { return wave_ext_u64<true>(x); }
 
