@@ -492,6 +492,10 @@ def main() -> int:
         cpu, parity = cpu_leg(plan, flags & ~api.OUT_NODES, args.cpu_seconds, per_node)
         cpu["value_unit_note"] = "simulated tile-nodes per second of the oracle (feasible simulations)"
 
+    # the library's rule: plain batches of at most 1024 records, or of machines of at most 64 SMs
+    team = name not in ("noc", "txn", "l2lru") and all(
+        b <= 1024 or plan.parts[i][4][:, 0].max() <= 64 for i, _, b in plan.launches)
+
     out = {
         "metric": "simulated tile-nodes/sec (batched) + simulations/sec; % of HBM roofline",
         "value": node_sims * K / wall,
@@ -510,7 +514,7 @@ def main() -> int:
                    "sims_per_step": sims,
                    "outputs": "per-node start/finish + makespan + status + digest" if per_node
                    else "makespan + status + digest",
-                   "parallelism": "one wavefront per simulation", "streams": len(streams),
+                   "parallelism": "one %s per simulation" % ("workgroup" if team else "wavefront"), "streams": len(streams),
                    "launches_per_step": launches_per_step},
         "simulations_per_s": sims * K / wall,
         "node_sims_per_step": node_sims,
@@ -522,7 +526,7 @@ def main() -> int:
                      "algorithmic_bytes_per_step": abytes,
                      "step_ms": mean_step * 1e3,
                      "kernel": {"noc": "gts_sim_wave", "txn": "gts_sim_window_txn",
-                                "l2lru": "gts_sim_window_lru"}.get(name, "gts_sim_window"),
+                                "l2lru": "gts_sim_window_lru"}.get(name, "gts_sim_team" if team else "gts_sim_window"),
                      "launch_ms": mean_launch * 1e3,
                      "per_launch_gbs": abytes / launches_per_step / mean_launch / 1e9,
                      "note": "achieved = algorithmic bytes per step / mean step time (HIP events; launches of a "
