@@ -128,7 +128,6 @@ struct Image {
   const NodeDev* tnodes;        // template records (succ: local index | bits)
   const uint32_t* tsucc;        // template successors beyond the records' inline ones
   const uint16_t* tindeg;       // in-degree per template record
-  const uint32_t* crec;         // compact template records, parallel to tnodes
   const uint8_t* cclass;        // class of each CTA of a templated kernel
   const uint16_t* tops;         // [n_tops] class x slot -> op id
   const uint32_t* tile;         // [N] tile of each load / store, numbered 0..n_tiles-1 (kGraphTiles), else null
@@ -140,6 +139,7 @@ struct Image {
   uint32_t n_nodes, n_edges, n_ctas, n_kernels, n_ops, props, n_tops;
   uint32_t n_tiles;             // distinct tiles
   uint32_t n_txn, n_lines;      // transactions of all addressed nodes, distinct lines
+  const uint32_t* crec;         // compact template records, parallel to tnodes
 };
 
 // Hardware record word indices (gts_hw_params field order).
@@ -214,7 +214,7 @@ struct Launch {
   uint32_t B, flags;
   uint32_t lds_optab;          // op table held in LDS (else in scratch)
   uint32_t lds_words_servers;  // words of per-SM server state reserved in LDS
-  uint32_t retry_only;         // general kernel: run only simulations marked kStatusRetry
+  uint32_t retry_only;         // windowed and general kernels: run only simulations marked kStatusRetry
   uint32_t max_nsm;            // largest n_sm of the batch
   uint32_t max_nsub;           // largest n_subpart of the batch
   uint32_t qp;                 // windowed kernel: later ready entries per lane held in LDS
