@@ -784,9 +784,9 @@ uint32_t device_cus() {
 // 4096 records of 64-192 SMs are faster too when nothing else runs (that GEMM
 // 10.2 / 8.4 ms), but the GEMM design sweep, whose launches overlap on two
 // streams, ran at 9.5e9 against 1.02e10 tile-nodes/s.
-bool team_batch(uint32_t mode, uint32_t B, uint32_t max_nsm) {
+bool team_batch(uint32_t B, uint32_t max_nsm) {
   constexpr uint32_t kTeamMost = 1024;
-  return mode == gts::kWinPlain && (B <= kTeamMost || max_nsm <= 64u);
+  return B <= kTeamMost || max_nsm <= 64u;
 }
 
 // LDS one workgroup may have on the current device (0 if it cannot be queried).
@@ -929,19 +929,23 @@ int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_
     windowed = bytes(qp) <= kLdsBudget;
     lds_window = bytes(qp);
   }
-  // GTS_KERNEL=window / team (diagnostics): only that kernel, so simulations
-  // it hands back keep their internal retry status.
+  // GTS_KERNEL=window / team (diagnostics): only that kernel, where it can run
+  // the batch (the team kernel: plain mode, LDS that fits the device), so
+  // simulations it hands back keep their internal retry status.
   const bool window_only = windowed && force && std::strcmp(force, "window") == 0;
-  const bool team_only = windowed && force && std::strcmp(force, "team") == 0;
+  bool team_only = windowed && force && std::strcmp(force, "team") == 0;
+  bool team = windowed && !window_only && mode == gts::kWinPlain && (team_only || team_batch(B, max_nsm));
   hipError_t e = hipSuccess;
-  if (windowed && !window_only && (team_only || team_batch(mode, B, max_nsm))) {
+  if (team) {
     gts::Launch T = L;
     const uint32_t lds_team = team_sizes(g, T, wstride);
-    if (lds_team <= device_lds()) {
+    team = lds_team <= device_lds();
+    if (team) {
       e = gts::launch_team(T, lds_team, st);
       L.retry_only = 1;
     }
   }
+  team_only = team_only && team;
   if (e == hipSuccess && windowed && !team_only) {
     e = gts::launch_window(L, lds_window, st);
     L.retry_only = 1;

@@ -125,3 +125,18 @@ def test_team_hands_back_overflow(torch_cuda, monkeypatch):
     res = api.simulate(api.upload(g), hws, ALL)
     torch_cuda.cuda.synchronize()
     compare(g, hws, ALL, api.to_numpy(res))
+
+
+@pytest.mark.parametrize("kind", ["tiles", "addresses"])
+def test_team_forced_on_other_modes(torch_cuda, kind, monkeypatch):
+    """GTS_KERNEL=team takes no graph whose loads go through the LRU L2 or are
+    split into transactions: the team kernel has neither, so the normal path
+    runs them and every cycle is the oracle's."""
+    g = W.gemm(512, 512, 512, 128, 128, 32, 2, tiles=True) if kind == "tiles" else \
+        W.gemm_addressed(512, 512, 512, 128, 128, 32, 2)
+    hws = np.stack([H.preset("H100", n_sm=s, l2_lines=H.l2_lines(mib)) for s in (4, 132) for mib in (0.01, 0.25)])
+    note(f"team forced on {kind} N={g.n_nodes}")
+    monkeypatch.setenv("GTS_KERNEL", "team")
+    res = api.simulate(api.upload(g), hws, ALL)
+    torch_cuda.cuda.synchronize()
+    compare(g, hws, ALL, api.to_numpy(res))
