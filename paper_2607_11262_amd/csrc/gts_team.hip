@@ -129,8 +129,9 @@ __device__ __forceinline__ MP wave_incl_mp(MP c) {
   c = after(dpp_mp<kRowBcast31, 0xC>(c), c);
   return c;
 }
-// Barrier that orders LDS only: global memory is private to a thread's SM,
-// atomic, or handed over at a full barrier.
+// Barrier that orders LDS only.  Global memory is private to a thread's SM,
+// atomic, handed over at a full barrier, or written by a thread that waits for
+// its write before it comes here (push, ret_push).
 template <uint32_t NW>
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -215,11 +216,14 @@ struct TSim {
     else
       q_g[(i - QF) * TH + t] = k;
   }
-  // outside the local phase any thread may push to any SM's list
+  // outside the local phase any thread may push to any SM's list; its owner
+  // reads it behind a barrier that orders LDS only, so an entry that goes to
+  // scratch is waited for here
   __device__ __forceinline__ void push(uint32_t t, uint32_t cyc, uint32_t low) {
     const uint32_t i = lds_add(&q_cnt[t], 1u);
     if (i < qcap) {
       q_set(t, i, ((uint64_t)cyc << 32) | low);
+      if (i >= QF) mem_wait();
       lds_min(&q_min[t], cyc);
     } else {
       bad |= kBadQueue;

@@ -140,3 +140,49 @@ def test_team_forced_on_other_modes(torch_cuda, kind, monkeypatch):
     res = api.simulate(api.upload(g), hws, ALL)
     torch_cuda.cuda.synchronize()
     compare(g, hws, ALL, api.to_numpy(res))
+
+
+def _many_releases_into_one_cta(n_sources, per_source):
+    """One kernel: source CTAs of loads, and a last CTA whose nodes each wait
+    for one of those loads (and join in a store)."""
+    from paper_2607_11262_amd.gen.graph import ALU, GLOAD, GSTORE, MISS, SYNC, GraphBuilder
+    b = GraphBuilder()
+    b.kernel(4, 0)
+    loads = []
+    for c in range(n_sources):
+        b.cta()
+        mine = [b.node(GLOAD, 512 + 64 * ((c + i) % 5), 0xF, MISS if i % 2 else 0) for i in range(per_source)]
+        out = b.node(GSTORE, 256, 0xF, MISS)
+        for u in mine:
+            b.edge(u, out)
+        loads += mine
+    b.cta()
+    heads = [b.node(ALU, 256, 0xF) for _ in loads]
+    join = b.node(SYNC, 0, 0xF)
+    out = b.node(GSTORE, 256, 0xF)
+    for u in heads:
+        b.edge(u, join)
+    b.edge(join, out)
+    for u, v in zip(loads, heads):
+        b.edge(u, v)
+    return b.build("many_releases")
+
+
+@pytest.mark.parametrize("sms", [70, 130, 200, 256])
+def test_team_releases_past_the_lds_list(torch_cuda, sms, monkeypatch):
+    """Loads of CTAs on all waves ready the nodes of one CTA: its SM's list
+    runs past its part in LDS with entries that other waves write."""
+    g = _many_releases_into_one_cta(sms - 1, 1)
+    g2 = _many_releases_into_one_cta(16, 5)
+    for gr in (g, g2):
+        assert window_eligible(gr)
+        # a fast memory: many loads finish in one window
+        hws = np.stack([H.preset("H100", n_sm=sms, max_cta_per_sm=2, rate_l2=4096 << 16, rate_dram=4096 << 16,
+                                 lat_l2=200 + 50 * i, lat_dram=200 + 90 * i) for i in range(4)])
+        note(f"team releases n_sm={sms} N={gr.n_nodes}")
+        gpu, _, _ = run_team_only(torch_cuda, gr, hws, ALL, monkeypatch)
+        if gr is g2:
+            check(torch_cuda, gr, hws, ALL, monkeypatch, f"releases {sms}")
+        res = api.simulate(api.upload(gr), hws, ALL)  # the longer list is handed back where it does not fit
+        torch_cuda.cuda.synchronize()
+        compare(gr, hws, ALL, api.to_numpy(res))
