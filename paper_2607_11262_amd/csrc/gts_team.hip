@@ -129,6 +129,12 @@ __device__ __forceinline__ MP wave_incl_mp(MP c) {
   c = after(dpp_mp<kRowBcast31, 0xC>(c), c);
   return c;
 }
+// Cycles past the last one stay at 2^32 - 1, which is never due.  Were they to
+// wrap, they could come up again in the same window, where the counts beside
+// them in the state slots are no longer whole: each level of joins could be
+// ready twice as often as the one before.
+__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+
 // Barrier that orders LDS only.  Global memory is private to a thread's SM,
 // atomic, handed over at a full barrier, or written by a thread that waits for
 // its write before it comes here (push, ret_push).
@@ -881,9 +887,9 @@ struct TSim {
         const bool h = NS == 1 || ((held >> l) & 1u) != 0u;
         st = h && !nocont && busy[l] > st ? busy[l] : st;
       }
-      const uint32_t fr = st + od.x;
-      f = fr + (is_mem ? 0u : od.z);
-      bad |= fr < st || f < fr || f > kMaxCycle ? kBadOverflow : 0u;
+      const uint32_t fr = add_sat(st, od.x), s1 = add_sat(st, 1u);
+      f = add_sat(fr, is_mem ? 0u : od.z);
+      bad |= f > kMaxCycle ? kBadOverflow : 0u;
       bad |= f - t_cyc > kSlotMask ? kBadQueue : 0u;
 #pragma unroll
       for (uint32_t l = 0; l < NS; ++l) {
@@ -900,9 +906,9 @@ struct TSim {
       }
       lmem<uint32_t>* const sb = slots_of(low);
       const uint32_t keep = low & ~(((1u << nb) - 1u) << pb), cnt = a.z >> 28;
-      release_words<SPILL>(a, cnt, st + 1u, f, H, sb, keep);
+      release_words<SPILL>(a, cnt, s1, f, H, sb, keep);
       if (__ballot(cnt > 4u)) {
-        if (cnt > 4u) release_words<SPILL>(get4(rp + 1), cnt - 4u, st + 1u, f, H, sb, keep);
+        if (cnt > 4u) release_words<SPILL>(get4(rp + 1), cnt - 4u, s1, f, H, sb, keep);
       }
       v = node_of(low);
     }
@@ -932,9 +938,9 @@ struct TSim {
       c = (uint32_t)(key >> 32);
       const lmem<uint4>* const rp = rec_at(low);
       const uint4 a = get4(rp), w = get4(rp + 1);
-      const uint32_t e = c + od.x, g = e > m ? e : m;
-      f = g + od.z;
-      bad |= e < c || f < g || f > kMaxCycle ? kBadOverflow : 0u;
+      const uint32_t e = add_sat(c, od.x), g = e > m ? e : m;
+      f = add_sat(g, od.z);
+      bad |= f > kMaxCycle ? kBadOverflow : 0u;
       bad |= f - t_cyc > kSlotMask ? kBadQueue : 0u;
       release_words<SPILL>(w, a.w >> 29, f, f, 0u, slots_of(low), low & ~(((1u << nb) - 1u) << pb));
       if (a.y >> 31) ret_push(f, low & ((1u << pb) - 1u));  // the sink finishes last

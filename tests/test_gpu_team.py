@@ -186,3 +186,48 @@ def test_team_releases_past_the_lds_list(torch_cuda, sms, monkeypatch):
         res = api.simulate(api.upload(gr), hws, ALL)  # the longer list is handed back where it does not fit
         torch_cuda.cuda.synchronize()
         compare(gr, hws, ALL, api.to_numpy(res))
+
+
+def _late_diamonds(levels):
+    """A kernel that ends at cycle ~0xF0000000, then a templated one whose root
+    finishes past the last cycle, followed by levels of four nodes joined by
+    one.  The root's finish wraps to 0x08000000, below the window's end."""
+    from paper_2607_11262_amd.gen.graph import GLOAD, GSTORE, SYNC, TENSOR, GraphBuilder
+    b = GraphBuilder()
+    b.kernel(4, 0)
+    b.cta()
+    u = b.node(GLOAD, 64, 0xF)
+    for cls, work in ((SYNC, 0), (SYNC, 0), (SYNC, 0), (TENSOR, 0x3000), (GSTORE, 64)):
+        v = b.node(cls, work, 0xF)
+        b.edge(u, v)
+        u = v
+    b.kernel(4, 0)
+    for _ in range(2):
+        b.cta()
+        x = b.node(TENSOR, 0x1800, 0xF)
+        for _l in range(levels):
+            y = [b.node(TENSOR, 0, 0xF) for _ in range(4)]
+            j = b.node(TENSOR, 0, 0xF)
+            for v in y:
+                b.edge(x, v)
+                b.edge(v, j)
+            x = j
+        out = b.node(GSTORE, 64, 0xF)
+        b.edge(x, out)
+    return b.build("late_diamonds")
+
+
+def test_team_gives_up_past_the_last_cycle(torch_cuda, monkeypatch):
+    """A simulation that passes the last cycle in a kernel run from LDS ends
+    there: its cycles stay past the end.  (Were they to wrap, each level of
+    joins could become ready twice as often as the one before.)"""
+    g = _late_diamonds(40)
+    assert window_eligible(g) and api.templates(g)["templated_kernels"] == 1
+    hws = np.stack([H.toy(n_sm=s, n_subpart=1, rate_tensor=1, lat_tensor=0, lat_sync=1 << 30, max_cta_per_sm=2)
+                    for s in (1, 2, 65)])
+    gpu, _, _ = run_team_only(torch_cuda, g, hws, ALL, monkeypatch)
+    assert np.all(gpu[2] == STATUS_RETRY)
+    res = api.simulate(api.upload(g), hws, ALL)
+    torch_cuda.cuda.synchronize()
+    compare(g, hws, ALL, api.to_numpy(res))
+    assert np.all(res.status.cpu().numpy() == api.SIM_OVERFLOW)
