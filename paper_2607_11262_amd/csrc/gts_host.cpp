@@ -77,6 +77,7 @@ struct KTemplate {
   uint32_t t_base = 0;  // first template record
   uint32_t t_ops = 0;   // first class x slot entry
   uint32_t nslot = 0;
+  uint32_t nclass = 0;  // op classes of its CTAs
   uint32_t tsucc = 0;   // first template successor
   int32_t sink = -1;    // local index of the template's retiring sink, or -1
   uint32_t slots = 0;   // state slots per CTA of its compact records, 0: it has none
@@ -109,15 +110,12 @@ struct Derived {
 // Kernels that would take the class x slot table past kMaxTops entries, or
 // that have more than 255 classes, stay expanded.  GTS_TEMPLATES=0 turns the
 // detection off.
-void compact_template(const gts_graph_host* h, Derived* d, uint32_t u0, KTemplate& t);
-
 void find_templates(const gts_graph_host* h, Derived* d) {
   const uint32_t K = h->n_kernels, C = h->n_ctas;
   d->ktmpl.assign(K, KTemplate());
   d->cclass.assign(C, 0);
   d->tslot.clear();
   d->tops.clear();
-  d->crec.clear();
   d->n_tnodes = d->n_tsucc = 0;
   if (const char* e = std::getenv("GTS_TEMPLATES"))
     if (std::strcmp(e, "0") == 0) return;
@@ -180,6 +178,7 @@ void find_templates(const gts_graph_host* h, Derived* d) {
     t.t_base = d->n_tnodes;
     t.t_ops = (uint32_t)d->tops.size();
     t.nslot = nslot;
+    t.nclass = nclass;
     t.tsucc = d->n_tsucc;
     for (uint32_t q = 0; q < nclass; ++q)
       for (uint32_t s = 0; s < nslot; ++s) d->tops.push_back(slot_cols[s][q]);
@@ -227,23 +226,21 @@ void find_templates(const gts_graph_host* h, Derived* d) {
     }
     d->n_tnodes += n;
     d->n_tsucc += h->succ_ptr[nb[c0] + n] - h->succ_ptr[nb[c0]];
-    d->crec.resize((size_t)d->n_tnodes * gts::kCompactWords, 0);
-    compact_template(h, d, nb[c0], t);
   }
 }
 
-// Compact records of a template (gts_dev.h), if it fits them: state slots for
+// Compact records of template t (gts_dev.h), if it fits them: state slots for
 // its nodes of two or more in-edges, each node into the first slot whose last
 // node is an ancestor of, or is, every predecessor of it.
-void compact_template(const gts_graph_host* h, Derived* d, uint32_t u0, KTemplate& t) {
+void compact_template(const gts_graph_host* h, Derived* d, uint32_t u0, uint32_t nclass, KTemplate& t) {
   const uint32_t n = t.t_n;
   if (n > gts::kCompactMaxNodes || t.sink < 0) return;
   auto deg = [&](uint32_t i) { return h->succ_ptr[u0 + i + 1] - h->succ_ptr[u0 + i]; };
   auto edge = [&](uint32_t i, uint32_t j) { return h->succ[h->succ_ptr[u0 + i] + j]; };
+  auto target = [&](uint32_t i, uint32_t j) { return (edge(i, j) & GTS_EDGE_TARGET_MASK) - u0; };
   auto at_issue = [&](uint32_t i, uint32_t j) { return (edge(i, j) >> GTS_EDGE_KIND_SHIFT) == GTS_EDGE_ORDER; };
-  std::vector<std::vector<uint32_t>> pred(n);
+  std::vector<uint32_t> indeg(n, 0);
   std::vector<uint8_t> mem(n);
-  const uint32_t nclass = ((uint32_t)d->tops.size() - t.t_ops) / t.nslot;
   for (uint32_t i = 0; i < n; ++i) {
     const uint16_t* op = &d->tops[t.t_ops + d->tslot[t.t_base + i]];
     mem[i] = is_memory(h->op_cls[op[0]]);
@@ -251,65 +248,82 @@ void compact_template(const gts_graph_host* h, Derived* d, uint32_t u0, KTemplat
       if ((bool)is_memory(h->op_cls[op[q * t.nslot]]) != (bool)mem[i]) return;
     uint32_t issue = 0;
     for (uint32_t j = 0; j < deg(i); ++j) {
-      pred[(edge(i, j) & GTS_EDGE_TARGET_MASK) - u0].push_back(i);
+      ++indeg[target(i, j)];
       issue += at_issue(i, j);
     }
     if (mem[i] ? issue > 4u || deg(i) - issue > 4u : deg(i) > 8u) return;
   }
-  // topological order, with each node's ancestors
+  // In topological order, each node passes its ancestors and itself on to its
+  // successors.  all: the nodes that are an ancestor of, or are, every
+  // predecessor met so far.  A node's sets are complete when it comes up, so
+  // the first slot whose last node is in its `all` is found then, from the
+  // bits it shares with the slots' last nodes.
   const uint32_t words = (n + 63) / 64;
-  std::vector<uint64_t> anc((size_t)n * words, 0);
-  std::vector<uint32_t> order, left(n);
+  std::vector<uint64_t> anc((size_t)n * words, 0), all((size_t)n * words, ~0ull), lasts(words, 0);
+  std::vector<uint32_t> order, left = indeg, slot(n, 0);
   order.reserve(n);
   for (uint32_t i = 0; i < n; ++i) {
-    if (pred[i].size() > gts::kCompactMaxIndeg) return;
-    left[i] = (uint32_t)pred[i].size();
+    if (indeg[i] > gts::kCompactMaxIndeg) return;
     if (!left[i]) order.push_back(i);
   }
+  uint32_t used = 0;
   for (uint32_t q = 0; q < order.size(); ++q) {
     const uint32_t i = order[q];
-    uint64_t* a = &anc[(size_t)i * words];
-    for (uint32_t p : pred[i]) {
-      const uint64_t* b = &anc[(size_t)p * words];
-      for (uint32_t w = 0; w < words; ++w) a[w] |= b[w];
-      a[p / 64] |= 1ull << (p % 64);
+    uint64_t* const a = &anc[(size_t)i * words];
+    if (indeg[i] >= 2) {
+      uint32_t s = used, node = 0;
+      for (uint32_t w = 0; w < words; ++w)
+        for (uint64_t m = all[(size_t)i * words + w] & lasts[w]; m; m &= m - 1) {
+          const uint32_t v = w * 64 + (uint32_t)__builtin_ctzll(m);
+          if (slot[v] < s) s = slot[v], node = v;
+        }
+      if (s == used)
+        ++used;
+      else
+        lasts[node / 64] &= ~(1ull << (node % 64));
+      if (used + 2u > gts::kCompactMaxSlots) return;
+      slot[i] = s;
+      lasts[i / 64] |= 1ull << (i % 64);
     }
+    a[i / 64] |= 1ull << (i % 64);
     for (uint32_t j = 0; j < deg(i); ++j) {
-      const uint32_t v = (edge(i, j) & GTS_EDGE_TARGET_MASK) - u0;
+      const uint32_t v = target(i, j);
+      for (uint32_t w = 0; w < words; ++w) {
+        anc[(size_t)v * words + w] |= a[w];
+        all[(size_t)v * words + w] &= a[w];
+      }
       if (--left[v] == 0) order.push_back(v);
     }
   }
-  std::vector<uint32_t> slot(n, 0), last;  // last: the latest node of each slot
-  for (uint32_t i : order) {
-    if (pred[i].size() < 2) continue;
-    uint32_t s = 0;
-    for (; s < last.size(); ++s) {
-      const uint32_t a = last[s];
-      bool ok = true;
-      for (uint32_t p : pred[i]) ok = ok && (p == a || ((anc[(size_t)p * words + a / 64] >> (a % 64)) & 1u));
-      if (ok) break;
-    }
-    if (s == last.size()) last.push_back(0);
-    last[s] = i;
-    slot[i] = s;
-  }
-  const uint32_t zero = (uint32_t)last.size(), none = zero + 1u;
-  if (none + 1u > gts::kCompactMaxSlots) return;
+  const uint32_t zero = used, none = zero + 1u;
   t.slots = none + 1u;
   for (uint32_t i = 0; i < n; ++i) {
     uint32_t* r = &d->crec[(size_t)(t.t_base + i) * gts::kCompactWords];
     for (uint32_t w = 0; w < gts::kCompactWords; ++w) r[w] = none << 12;
     uint32_t first = 0, second = 0;
     for (uint32_t j = 0; j < deg(i); ++j) {
-      const uint32_t v = (edge(i, j) & GTS_EDGE_TARGET_MASK) - u0, in = (uint32_t)pred[v].size();
+      const uint32_t v = target(i, j);
       const uint32_t w = mem[i] && !at_issue(i, j) ? 4u + second++ : first++;
-      r[w] = v | (in > 1u ? slot[v] : zero) << 12 | in << 22 | (at_issue(i, j) ? 1u << 27 : 0u);
+      r[w] = v | (indeg[v] > 1u ? slot[v] : zero) << 12 | indeg[v] << 22 | (at_issue(i, j) ? 1u << 27 : 0u);
     }
     const uint32_t op = d->tslot[t.t_base + i];
     r[0] |= (op & 15u) << 28;
     r[1] |= (op >> 4) << 28 | (t.sink == (int32_t)i ? (uint32_t)gts::kRecSink << 31 : 0u);
     r[2] |= first << 28;
     r[3] |= (mem[i] ? 1u << 28 : 0u) | second << 29;
+  }
+}
+
+// Compact records of every template.  Only an upload needs them (the image's
+// size does not depend on what they hold), and templates of more than 1022
+// nodes waiting for several in-edges at once give up there: built for every
+// size query, slot by slot, they took 2 CTAs of 1944 nodes from 0.30 to
+// 1.8 ms per query or upload and 2 of 3886 from 0.57 to 7.0 ms.
+void compact_templates(const gts_graph_host* h, Derived* d) {
+  d->crec.assign((size_t)d->n_tnodes * gts::kCompactWords, 0);
+  for (uint32_t k = 0; k < h->n_kernels; ++k) {
+    KTemplate& t = d->ktmpl[k];
+    if (t.t_n) compact_template(h, d, h->cta_node_begin[h->kernel_cta_begin[k]], t.nclass, t);
   }
 }
 
@@ -614,7 +628,7 @@ ImageLayout image_layout(const gts_graph_host* h, const Derived& d) {
   L.tindeg = off;
   off = align_up(off + (uint64_t)d.n_tnodes * 2, gts::kAlign);
   L.crec = off;
-  off = align_up(off + (uint64_t)d.crec.size() * 4, gts::kAlign);
+  off = align_up(off + (uint64_t)d.n_tnodes * gts::kCompactWords * 4, gts::kAlign);
   L.cclass = off;
   off = align_up(off + (uint64_t)h->n_ctas, gts::kAlign);
   L.tops = off;
@@ -1051,6 +1065,7 @@ int gts_graph_upload(const gts_graph_host* h, void* dev_image, uint64_t dev_byte
   std::vector<uint8_t> img;
   try {
     img.assign(L.total, 0);
+    compact_templates(h, &d);
   } catch (const std::bad_alloc&) {
     return fail(GTS_E_ARG, "host staging of %llu bytes failed", (unsigned long long)L.total);
   }
