@@ -1,5 +1,5 @@
-// Test harness: the host library's derivation of a graph, and its compact
-// template records, without a device (built with g++ beside the launch
+// Test harness: what the host library derives from a graph (compact template
+// records, bursts of ready nodes), without a device (built with g++ beside the launch
 // stand-ins of gts_host_only.cpp).
 #include "../paper_2607_11262_amd/csrc/gts_host.cpp"
 
@@ -10,6 +10,18 @@ extern "C" int64_t gts_test_words_after_check(const gts_graph_host* h) {
   int64_t n = (int64_t)d.crec.size();
   for (const KTemplate& t : d.ktmpl) n += t.slots;
   return n;
+}
+
+// Nodes that one event readies on one SM, at least.
+extern "C" int64_t gts_test_burst(const gts_graph_host* h) {
+  Derived d;
+  if (check_graph(h, &d)) return -1;
+  return h->n_nodes ? (int64_t)ready_burst(h, d) : 0;
+}
+
+// Whether a burst surely outgrows the team kernel's lists.
+extern "C" int gts_test_team_overflows(uint32_t burst, uint32_t qp, uint32_t max_nsm) {
+  return team_overflows(burst, qp, max_nsm);
 }
 
 // Per kernel {template nodes, first record, state slots}, then the record

@@ -188,6 +188,51 @@ def test_team_releases_past_the_lds_list(torch_cuda, sms, monkeypatch):
         compare(gr, hws, ALL, api.to_numpy(res))
 
 
+def _fan_out(width, kind):
+    """CTAs of one node after another, then `width` nodes that one event
+    readies, on a CTA of its own per SM."""
+    from paper_2607_11262_amd.gen.graph import ALU, DATA, GLOAD, GSTORE, MISS, ORDER, SYNC, GraphBuilder
+    b = GraphBuilder()
+    b.kernel(4, 0)
+    for _ in range(4):
+        b.cta()
+        u = b.node(GLOAD, 256, 0xF, MISS)
+        for _i in range(8):
+            a, v = b.node(ALU, 64, 0xF), b.node(GLOAD, 256, 0xF)
+            b.edge(u, a)
+            b.edge(a, v)
+            u = v
+        if kind == "compute":
+            v = b.node(ALU, 64, 0xF)
+            b.edge(u, v)
+            u = v
+        mid = [b.node(ALU, 64 + i % 5, 0xF) for i in range(width)]
+        join, out = b.node(SYNC, 0, 0xF), b.node(GSTORE, 256, 0xF)
+        for m in mid:
+            b.edge(u, m, ORDER if kind == "issue" else DATA)
+            b.edge(m, join)
+        b.edge(join, out)
+        if kind == "issue":
+            b.edge(u, out)
+    return b.build("fan_out")
+
+
+@pytest.mark.parametrize("kind", ["issue", "completion", "compute"])
+def test_team_bursts(torch_cuda, kind, monkeypatch):
+    """What the rule that leaves such graphs to the windowed kernel rests on:
+    a burst past the lists is handed back by every simulation of the batch,
+    one that fits by none."""
+    for width, fits in ((60, True), (300, False)):
+        g = _fan_out(width, kind)
+        assert window_eligible(g)
+        hws = np.stack([H.preset("H100", n_sm=s, max_cta_per_sm=1) for s in (132, 256, 44, 4)])
+        gpu, _, _ = run_team_only(torch_cuda, g, hws, ALL, monkeypatch)
+        assert np.all((gpu[2] == STATUS_RETRY) != fits), (width, gpu[2])
+        res = api.simulate(api.upload(g), hws, ALL)
+        torch_cuda.cuda.synchronize()
+        compare(g, hws, ALL, api.to_numpy(res))
+
+
 def _late_diamonds(levels):
     """A kernel that ends at cycle ~0xF0000000, then a templated one whose root
     finishes past the last cycle, followed by levels of four nodes joined by

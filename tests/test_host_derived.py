@@ -1,5 +1,6 @@
-"""Compact template records on the CPU: what they decode to, the sharing of
-state slots under random event orders, and that only an upload builds them."""
+"""What the host derives for the team kernel, on the CPU: compact template
+records (what they decode to, the sharing of state slots under random event
+orders, that only an upload builds them) and bursts of ready nodes."""
 import ctypes
 import os
 import subprocess
@@ -13,6 +14,7 @@ from paper_2607_11262_amd.gen.graph import ALU, DATA, GLOAD, GSTORE, ORDER, SYNC
 from paper_2607_11262_amd.gen.rng import SplitMix64
 from single_sink import single_sink_graph
 from templated import templated_graph
+from windowed import windowed_graph
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2607_11262_amd", "csrc")
@@ -22,10 +24,11 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2607_11262_amd", "csrc")
 def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("compact") / "compact.so")
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
-                           "-I/opt/rocm/include", os.path.join(HERE, "compact_records.cpp"),
+                           "-I/opt/rocm/include", os.path.join(HERE, "host_derived.cpp"),
                            os.path.join(CSRC, "gts_host_only.cpp"), "-L/opt/rocm/lib", "-lamdhip64", "-o", out])
     L = ctypes.CDLL(out)
     L.gts_test_words_after_check.restype = L.gts_test_compact.restype = ctypes.c_int64
+    L.gts_test_burst.restype = ctypes.c_int64
     L.gts_test_compact.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_uint64]
     return L
 
@@ -179,3 +182,33 @@ def test_queries_build_no_records(lib):
         h, _keep = api._host_struct(g)
         assert lib.gts_test_words_after_check(ctypes.byref(h)) == 0
         assert any(s for _, s, _ in compact(lib, g))
+
+
+def burst(g):
+    """Nodes that one event readies on one SM, at least, written out."""
+    ptr, succ = np.asarray(g.succ_ptr, np.int64), np.asarray(g.succ, np.int64)
+    tgt, kind = succ & 0x3FFFFFFF, succ >> 30
+    src = np.repeat(np.arange(g.n_nodes), np.diff(ptr))
+    cta = np.repeat(np.arange(len(g.cta_node_begin) - 1), np.diff(np.asarray(g.cta_node_begin, np.int64)))
+    indeg = np.bincount(tgt, minlength=g.n_nodes)
+    mem = np.isin(np.asarray(g.op_cls)[np.asarray(g.node_op, np.int64)], (GLOAD, GSTORE))
+    alone = (indeg[tgt] == 1) & (cta[src] == cta[tgt])
+    issue = mem[src] & (kind == ORDER)
+    counts = [np.bincount(cta[indeg == 0]), np.bincount(src[alone & issue]), np.bincount(src[alone & ~issue])]
+    return max(int(c.max()) if c.size else 0 for c in counts)
+
+
+def test_burst(lib):
+    def of(g):
+        h, _keep = api._host_struct(g)
+        return lib.gts_test_burst(ctypes.byref(h))
+    for seed in range(100):
+        g = windowed_graph(SplitMix64(seed, 17))
+        assert of(g) == burst(g), f"seed {seed}"
+    g = W.splitkv_decode(batch=6, kv_min=64, kv_max=4096, seed=9)
+    assert of(g) == burst(g) > 0
+    assert of(_joins(300)) == 300  # its loads
+    # the pending node beside a full list of qp + 240 / waves entries
+    for sms, share in ((1, 240), (64, 240), (65, 120), (132, 80), (256, 60)):
+        assert not lib.gts_test_team_overflows(8 + share + 1, 8, sms)
+        assert lib.gts_test_team_overflows(8 + share + 2, 8, sms)
