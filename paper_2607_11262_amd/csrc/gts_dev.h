@@ -316,8 +316,11 @@ constexpr uint32_t kTeamCtl = kTeamExch + 32u;
 constexpr uint32_t kTeamNextCta = kTeamCtl, kTeamFree = kTeamCtl + 13u;
 constexpr uint32_t kTeamRed = kTeamCtl + 16u;      // two windows' words {earliest ready or arrival, retirement}
 constexpr uint32_t kTeamRetCnt = kTeamRed + 4u, kTeamRetMin = kTeamRetCnt + 1u;
-constexpr uint32_t kTeamFixedInit = kTeamRetMin + 1u - kTeamCtl;
-constexpr uint32_t kTeamSpare = (kTeamRetMin + 1u + 3u) & ~3u;  // four words for writes of lanes with nothing to write
+// counts for the counter block: kernels run from LDS, batches served in
+// doubles, batches ordered by 64-bit keys
+constexpr uint32_t kTeamCount = kTeamRetMin + 1u;
+constexpr uint32_t kTeamFixedInit = kTeamCount + 3u - kTeamCtl;
+constexpr uint32_t kTeamSpare = (kTeamCount + 3u + 3u) & ~3u;  // four words for writes of lanes with nothing to write
 constexpr uint32_t kTeamFixed = kTeamSpare + 4u;
 constexpr uint32_t kTeamLog = 128;    // finished nodes per wave waiting for their outputs (three words each)
 static_assert(kTeamKey32 % 4 == 0 && kTeamSorted % 4 == 0 && kTeamExch % 4 == 0 && kTeamCtl % 2 == 0 &&

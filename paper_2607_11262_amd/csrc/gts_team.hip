@@ -344,6 +344,7 @@ struct TSim {
   // zeroed state slots.
   __device__ __forceinline__ void stage_template() {
     if (hot) {
+      if (x == 0) lds()[kTeamCount] += 1u;
       const gmem<const uint32_t>* src = (const gmem<const uint32_t>*)G.crec + (uint64_t)t_base * kCompactWords;
       for (uint32_t i = x; i < t_n * (kCompactWords / 4u); i += 64u * nw) {
         const uint4 w = ld4(src + 4u * i);
@@ -1686,6 +1687,7 @@ __device__ __forceinline__ void team_body(const Launch& L) {
             }
           }
         } else {
+          if (i == 0) lds[kTeamCount + 2u] += 1u;
           for (uint32_t j = 0; j < M; j += 8) {
             uint4 kk[4];
 #pragma unroll
@@ -1708,6 +1710,7 @@ __device__ __forceinline__ void team_body(const Launch& L) {
         else
           S.template serve<4, true>(M, wbase, cw, T);
       } else {
+        if (x == 0) lds[kTeamCount + 1u] += 1u;
         S.template serve<4, false>(M, wbase, cw, T);
       }
       // this SM's arrivals, in order
@@ -1782,7 +1785,7 @@ __device__ __forceinline__ void team_body(const Launch& L) {
     for (uint32_t i = 0; i < 5; ++i) stats[6 + i] = ck[i];
     stats[11] = S.nw;  // wavefronts of the simulation
     stats[12] = why;
-    stats[13] = stats[14] = stats[15] = 0;
+    for (uint32_t i = 0; i < 3; ++i) stats[13 + i] = lds[kTeamCount + i];
     int32_t st = GTS_SIM_OK;
     if (why & 1u)
       st = kStatusRetry;

@@ -23,10 +23,11 @@ def torch_cuda():
     return torch
 
 
-def run_team_only(torch, g, hws, flags, monkeypatch):
-    """As run_window_only, with GTS_KERNEL=team; returns the outputs and, per
-    simulation, the windows and the wavefronts its counter block reports."""
-    monkeypatch.setenv("GTS_KERNEL", "team")
+def run_counted(torch, g, hws, flags, monkeypatch, kernel="team"):
+    """One launch with GTS_KERNEL=kernel (None: the normal path); returns the
+    outputs and every simulation's counter block."""
+    if kernel:
+        monkeypatch.setenv("GTS_KERNEL", kernel)
     try:
         dg = api.upload(g)
         hs = api.upload_hw(hws)
@@ -38,10 +39,18 @@ def run_team_only(torch, g, hws, flags, monkeypatch):
         torch.cuda.synchronize()
         blk = scratch[:B * stride].view(B, stride)[:, stride - STATS_BYTES:].contiguous().view(torch.int64).cpu().numpy()
     finally:
-        monkeypatch.delenv("GTS_KERNEL")
+        if kernel:
+            monkeypatch.delenv("GTS_KERNEL")
     cyc, mk, st, dg_ = out
     return (cyc.cpu().numpy().view(np.uint32) if cyc is not None else None, mk.cpu().numpy().view(np.uint32),
-            st.cpu().numpy(), dg_.cpu().numpy().view(np.uint64) if dg_ is not None else None), blk[:, 0], blk[:, 11]
+            st.cpu().numpy(), dg_.cpu().numpy().view(np.uint64) if dg_ is not None else None), blk
+
+
+def run_team_only(torch, g, hws, flags, monkeypatch):
+    """The outputs of the team kernel alone and, per simulation, the windows
+    and the wavefronts its counter block reports."""
+    gpu, blk = run_counted(torch, g, hws, flags, monkeypatch)
+    return gpu, blk[:, 0], blk[:, 11]
 
 
 def check(torch, g, hws, flags, monkeypatch, what):
