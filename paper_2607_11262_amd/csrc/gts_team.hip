@@ -1762,11 +1762,13 @@ __device__ __forceinline__ void team_body(const Launch& L) {
     e[3] = nf;
     e[4] = ni;
     e[5] = (queue ? 1u : 0u) | (ovf ? 2u : 0u);
+    e[6] = steps;
   }
   __syncthreads();
   if (x == 0) {
     uint64_t dsum = 0;
     uint32_t mmax = 0, fsum = 0, isum = 0, why = 0;
+    uint64_t ssum = 0;
     for (uint32_t w = 0; w < S.nw; ++w) {
       const lmem<uint32_t>* const e = fin + w * 8u;
       dsum += ((uint64_t)e[1] << 32) | e[0];
@@ -1774,10 +1776,11 @@ __device__ __forceinline__ void team_body(const Launch& L) {
       fsum += e[3];
       isum += e[4];
       why |= e[5];
+      ssum += e[6];
     }
     uint64_t* stats = reinterpret_cast<uint64_t*>(sim + L.layout.stride - kStatsBytes);
     stats[0] = windows;
-    stats[1] = steps;
+    stats[1] = ssum;  // of all waves, as the nodes issued
     stats[2] = isum;
     stats[3] = arrivals;
     stats[4] = ctl[1];

@@ -171,3 +171,23 @@ def test_wide_ids_are_ordered_by_64_bits(torch_cuda, monkeypatch):
     small = W.gemm(512, 512, 512, 128, 128, 32, 2)
     blk, _ = on_team(torch_cuda, small, hws, ALL, monkeypatch, "short ids")
     assert np.all(blk[:, BY_64_BITS] == 0)
+
+
+def test_steps_of_all_waves_are_counted(torch_cuda, monkeypatch):
+    """Three CTAs on SMs of three waves, one of them short: with one busy SM
+    per wave every step issues one node."""
+    b = GraphBuilder()
+    b.kernel(4, 0)
+    for n in (2, 30, 11):
+        b.cta()
+        u = b.node(GLOAD, 256, 0xF)
+        for i in range(n):
+            v = b.node(GLOAD if i % 3 == 0 else ALU, 256, 0xF)
+            b.edge(u, v)
+            u = v
+        v = b.node(GSTORE, 256, 0xF)
+        b.edge(u, v)
+    g = b.build("three_chains")
+    hws = np.stack([H.preset("H100", n_sm=132), H.preset("H100", n_sm=192)])
+    blk, _ = on_team(torch_cuda, g, hws, ALL, monkeypatch, "three chains")
+    assert np.all(blk[:, 2] == g.n_nodes) and np.all(blk[:, 1] == blk[:, 2])
