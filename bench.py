@@ -252,6 +252,23 @@ class Plan:
         return ([a.elapsed_time(z) * 1e-3 for a, z in step_ev], [a.elapsed_time(z) * 1e-3 for a, z in launch_ev],
                 wall)
 
+    def counter_blocks(self, api, torch, scratch, i, first, b):
+        """The counter blocks that a launch (graph i, b records from `first`)
+        left at the end of its simulations' scratch slices, of its feasible
+        simulations."""
+        dg, _, (_, _, st, _), _, _ = self.parts[i]
+        stride = api.scratch_bytes(dg, 2, api.OUT_DIGEST) - api.scratch_bytes(dg, 1, api.OUT_DIGEST)
+        blk = scratch[:b * stride].view(b, stride)[:, stride - 128:].contiguous().view(torch.int64).cpu().numpy()
+        return blk[(st[first:first + b] == 0).cpu().numpy()]
+
+    def last_on_team(self, api, torch):
+        """Whether the team kernel finished the last launch of every stream:
+        word 11 of its counter block is the simulation's wavefronts (the
+        windowed kernel's is 0)."""
+        last = {k % len(self.streams): launch for k, launch in enumerate(self.launches)}
+        return all(bool(np.all(self.counter_blocks(api, torch, self.scratches[k], *launch)[:, 11] > 0))
+                   for k, launch in last.items())
+
     def feasible(self):
         """Per graph: its feasible records (an infeasible simulation stops
         after the residency check and simulates no node)."""
@@ -395,7 +412,7 @@ def main() -> int:
                          "passed from host memory per call (gts_simulate_batch) and results copied back, then "
                          "also with each graph uploaded from its host arrays every step")
     ap.add_argument("--phase-stats", action="store_true",
-                    help="after the timed region, report the windowed kernel's per-phase counters per graph")
+                    help="after the timed region, report the windowed or team kernel's per-phase counters per graph")
     ap.add_argument("--only-graph", type=int, default=-1,
                     help="diagnostics: simulate only this graph of the workload (index into its graphs)")
     ap.add_argument("--records", type=int, default=0,
@@ -445,6 +462,7 @@ def main() -> int:
         print(f"[bench] warmup step {k + 1}/{args.warmup} done", file=sys.stderr, flush=True)
     step_s, launch_s, wall = plan.timed(api, torch, args.steps)
     node_sims, sims, abytes, infeasible = plan.step_totals(per_node)
+    team = name not in ("noc", "txn", "l2lru") and plan.last_on_team(api, torch)
     K = args.steps
     if args.launch_log:
         with open(args.launch_log, "w") as f:
@@ -491,10 +509,6 @@ def main() -> int:
     if not args.no_cpu_baseline:
         cpu, parity = cpu_leg(plan, flags & ~api.OUT_NODES, args.cpu_seconds, per_node)
         cpu["value_unit_note"] = "simulated tile-nodes per second of the oracle (feasible simulations)"
-
-    # the library's rule: plain batches of at most 1024 records, or of machines of at most 64 SMs
-    team = name not in ("noc", "txn", "l2lru") and all(
-        b <= 1024 or plan.parts[i][4][:, 0].max() <= 64 for i, _, b in plan.launches)
 
     out = {
         "metric": "simulated tile-nodes/sec (batched) + simulations/sec; % of HBM roofline",
@@ -601,13 +615,14 @@ PHASE_COLUMNS = ("windows", "local_steps", "local_nodes", "memory_arrivals", "re
 
 
 def phase_stats(api, torch, plan):
-    """Where a windowed-kernel simulation spends its time: one untimed launch
-    of each graph's first chunk, then the per-simulation counter block the
-    kernel writes at the end of each simulation's scratch slice (windows,
-    local steps, nodes issued by them, memory arrivals, retirements, the
-    largest memory batch, and shader-clock ticks in the window scan,
-    retirement, local, ring-gather and memory phases), averaged over the
-    feasible simulations.  The clocks are read only in these launches
+    """Where a simulation of the windowed or the team kernel spends its time:
+    one untimed launch of each graph's first chunk, then the per-simulation
+    counter block the kernel writes at the end of each simulation's scratch
+    slice (windows, local steps -- of all its waves on the team kernel --,
+    nodes issued by them, memory arrivals, retirements, the largest memory
+    batch, and shader-clock ticks in the window scan, retirement, local,
+    ring-gather and memory phases, on the team kernel those of its first
+    wave), averaged over the feasible simulations.  The clocks are read only in these launches
     (GTS_WINDOW_CLOCKS): each read waits for every outstanding scalar and LDS
     access, which the timed launches avoid."""
     rows = {}
@@ -620,20 +635,19 @@ def phase_stats(api, torch, plan):
         seen.add(i)
         dg, hs, (cyc, mk, st, dgst), _, _ = plan.parts[i]
         flags = api.OUT_DIGEST
-        stride = api.scratch_bytes(dg, 2, flags) - api.scratch_bytes(dg, 1, flags)
         api.simulate_hwset_into(dg, hs, 0, b, flags, None, mk[:b], st[:b], dgst[:b], scratch, stream)
         torch.cuda.synchronize()
-        blk = scratch[:b * stride].view(b, stride)[:, stride - 128:].contiguous().view(torch.int64)
-        ok = (st[:b] == 0).cpu().numpy()
-        if not ok.any():
+        blk = plan.counter_blocks(api, torch, scratch, i, 0, b)
+        if not len(blk):
             continue
-        m = blk.cpu().numpy()[ok][:, :len(PHASE_COLUMNS)].astype(np.float64).mean(axis=0)
+        m = blk[:, :len(PHASE_COLUMNS)].astype(np.float64).mean(axis=0)
         row = {k: round(float(v), 1) for k, v in zip(PHASE_COLUMNS, m)}
         clk = m[6:11]
         row["nodes_per_local_step"] = round(float(m[2] / max(m[1], 1)), 2)
         row["arrivals_per_window"] = round(float(m[3] / max(m[0], 1)), 2)
         row["clk_share"] = {k[4:]: round(float(c / max(clk.sum(), 1)), 3) for k, c in zip(PHASE_COLUMNS[6:], clk)}
-        row["clk_per_local_step"] = round(float(m[8] / max(m[1], 1)))
+        waves = float(np.maximum(blk[:, 11], 1).mean())
+        row["clk_per_local_step"] = round(float(m[8] / max(m[1] / waves, 1)))  # of one wave
         row["clk_per_window_memory"] = round(float((m[9] + m[10]) / max(m[0], 1)))
         rows[str(i)] = row
         print(f"[bench] phase stats graph {i}: {json.dumps(row)}", file=sys.stderr, flush=True)
