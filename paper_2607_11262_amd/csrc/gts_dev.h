@@ -199,8 +199,8 @@ constexpr uint32_t kRetireCap = 8192;  // ... and in all (the rest spilled to sc
 constexpr uint32_t kWinCap = 256;      // memory arrivals (or retirements) per window
 constexpr uint32_t kWindowMax = 1024;  // longest window, in cycles
 constexpr uint64_t kWinMaxTileLines = 1ull << 22;  // LRU L2: lines of a tile the windowed kernel takes (below)
-constexpr int32_t kStatusRetry = 0x52455452;  // rerun this simulation on the general kernel
-constexpr uint64_t kStatsBytes = 128;          // windowed-kernel counters at the end of a slice
+constexpr int32_t kStatusRetry = 0x52455452;  // handed back: the team kernel's to the windowed one, its to the general one
+constexpr uint64_t kStatsBytes = 128;          // counters of the windowed or team kernel at the end of a slice
 
 struct Launch {
   Image img;
@@ -219,7 +219,7 @@ struct Launch {
   uint32_t max_nsub;           // largest n_subpart of the batch
   uint32_t qp;                 // windowed kernel: later ready entries per lane held in LDS
   uint32_t noc_words;          // general kernel: NoC server words after the per-SM servers
-  uint32_t clocks;             // windowed kernel: time its phases with the shader clock
+  uint32_t clocks;             // windowed and team kernels: time their phases with the shader clock
   uint32_t team_ring;          // team kernel: memory arrivals per SM held in LDS
   uint32_t team_ret;           // team kernel: pending retirements held in LDS
   uint32_t team_rec;           // team kernel: compact template records held in LDS

@@ -819,12 +819,16 @@ uint32_t device_cus() {
 // batch: it shortens a simulation's chain at the price of more wave
 // instructions, which pays while wave slots are idle, and on machines of at
 // most 64 SMs, where it has one wave too, at any size.  Measured, windowed /
-// team: split-KV decode (130,576 nodes) x 1024 records 91 / 39 ms, flash
-// attention (659,456) x 256 203 / 80 ms; 4096 records of 1, 16, 48 and 64 SMs:
-// 24,832-node GEMM 246 / 198, 23.6 / 18.4, 11.4 / 9.1 and 11.0 / 8.8 ms.
-// 4096 records of 64-192 SMs are faster too when nothing else runs (that GEMM
-// 10.2 / 8.4 ms), but the GEMM design sweep, whose launches overlap on two
-// streams, ran at 9.5e9 against 1.02e10 tile-nodes/s.
+// team, ms per launch alone and with launches overlapping on two streams,
+// 64-192 SMs: 24,832-node GEMM x 512 records 5.0 / 2.1 and 2.8 / 1.7, x 1024
+// 5.4 / 2.9 and 3.0 / 2.4, x 2048 6.0 / 5.7 and 4.6 / 4.5, x 4096 11.1 / 9.9
+// and 8.3 / 8.8; 50,176-node GEMM x 4096 32.2 / 27.3 and 32.0 / 27.2; split-KV
+// decode (130,576 nodes) x 1024 92 / 39 and 48 / 32.  At most 64 SMs: that
+// first GEMM x 4096 on 1-64 SMs 119 / 98 and 64 / 53, on 32-64 SMs 11.5 / 10.1
+// and 8.7 / 8.9; fused GEMM + SiLU on one SM x 4096 9.8 / 6.7 and 7.1 / 6.2.
+// Beyond 1024 the gain depends on the graph and on what else runs: the GEMM
+// design sweep (launches of 1364-4096 records on two streams) ran at 9.3e9
+// tile-nodes/s on the team kernel and at 1.02e10 on the windowed one.
 bool team_batch(uint32_t B, uint32_t max_nsm) {
   constexpr uint32_t kTeamMost = 1024;
   return B <= kTeamMost || max_nsm <= 64u;
@@ -846,10 +850,16 @@ uint32_t device_lds() {
   return (uint32_t)n;
 }
 
-// LDS bytes of a team launch.  The workgroups a CU will hold share its 160
-// KB; each first gets lists that the common step fits (eight entries beyond
-// its releases), then the compact template records, then the CTAs' state
-// slots, then longer lists.  What does not fit stays in global memory.
+// LDS bytes of a team launch.  The workgroups a CU will hold (as many as the
+// batch fills, at most twelve waves) share its 160 KB.  Each first gets ready
+// lists of 8 to 16 entries per SM (as fit half its share; a step that finds
+// fewer than eight of them free takes the path that may go past LDS), then the
+// compact template records, then the CTAs' state slots, then longer lists.
+// What does not fit stays in global memory, and with it a kernel whose records
+// and CTAs don't: at 129-192 SMs from the third workgroup per CU on, at 65-128
+// from the fourth.  There a launch takes a step: 24,832-node GEMM of 64-192
+// SMs x 512 records 1.97 ms from LDS, x 513 2.38 from global memory; attention
+// of 20,736 nodes 3.2 and 4.3 (windowed kernel: 5.0, 5.1, 7.7, 7.7).
 uint32_t team_sizes(const gts_graph* g, gts::Launch& L, uint32_t wstride) {
   const uint32_t TH = 64u * ((L.max_nsm + 63u) / 64u), P = g->img.n_ops + g->img.n_tops;
   const uint32_t cus = device_cus();
@@ -871,7 +881,7 @@ uint32_t team_sizes(const gts_graph* g, gts::Launch& L, uint32_t wstride) {
     if (bytes() > limit) L = old;
   };
   if (!g->compact.empty()) {
-    // lists that the common step fits, then the records of the shape with the
+    // lists as above, then the records of the shape with the
     // most nodes that leaves room for its places, then places, then the
     // records of smaller shapes come free
     const gts::Launch old = L;

@@ -26,10 +26,12 @@
 // of that chain and not the work per CU.  With one wave per simulation the
 // chain holds the packing of the taken nodes, two or three SMs per lane and a
 // 256-key sorting network; here each of them is spread over the waves or
-// gone.  Windowed kernel / this one: one 784-node GEMM 266 / 143 us, one
-// 82,944-node attention 16.2 / 4.6 ms, 64 decoder layers of 2.56 M nodes
-// 648 / 287 ms.  The windowed kernel takes fewer wave instructions per node,
-// and stays the faster one for large batches that overlap.
+// gone.  Windowed kernel / this one: one 784-node GEMM 266 / 141 us, one
+// 82,944-node attention 16.6 / 4.4 ms, 64 decoder layers of 2.56 M nodes
+// 641 / 279 ms.  The windowed kernel takes fewer wave instructions per node,
+// and stays the faster one for large batches that overlap.  The compiler
+// spills 306-347 scalar registers to lanes of the 147-153 vector ones (none to
+// memory), and reads them back lane by lane inside those chains.
 //
 // Memory: the ready list, memory-arrival ring, servers and counts of an SM
 // lie in LDS, strided by the workgroup's threads; what does not fit goes to

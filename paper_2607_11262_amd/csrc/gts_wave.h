@@ -109,6 +109,10 @@ struct Compose {  // f(x) = max(x, a) + o on int64
   int64_t a, o;
 };
 constexpr int64_t kNegCycle = -(int64_t(1) << 62);  // below every cycle: max(x, kNegCycle) = x
+// The DPP moves of dpp_c stay moves of their own in front of this subtraction:
+// in 64 bits it is a pair with a carry, which the compiler gives no DPP
+// operand (in 32 bits it does, wrongly for lanes without a source: the team
+// kernel's MaxPlus32 keeps them apart).
 __device__ __forceinline__ Compose compose(Compose f, Compose g) {  // g after f
   const int64_t ga = g.a - f.o;
   return Compose{f.a > ga ? f.a : ga, f.o + g.o};
