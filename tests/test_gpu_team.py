@@ -242,6 +242,19 @@ def test_team_bursts(torch_cuda, kind, monkeypatch):
         compare(g, hws, ALL, api.to_numpy(res))
 
 
+@pytest.mark.parametrize("width", [31, 32, 33, 38, 39, 40, 41, 100, 230])
+def test_team_lists_in_scratch(torch_cuda, width, monkeypatch):
+    """Ready lists on both sides of the end of their LDS part and of the eight
+    entries read at a time behind it, with the longest (4 simulations) and the
+    shortest LDS parts (2048)."""
+    for kind in ("issue", "compute"):
+        g = _fan_out(width, kind)
+        for B in (4, 2048):
+            hws = np.stack([H.preset("H100", n_sm=s, max_cta_per_sm=1) for s in (64, 1, 40, 3)] * (B // 4))
+            hws[:, H.FIELDS["rate_alu"]] += np.arange(B, dtype=np.uint32) % 61 << 12
+            check(torch_cuda, g, hws, api.OUT_DIGEST, monkeypatch, f"width {width} {kind} B {B}")
+
+
 def _late_diamonds(levels):
     """A kernel that ends at cycle ~0xF0000000, then a templated one whose root
     finishes past the last cycle, followed by levels of four nodes joined by
