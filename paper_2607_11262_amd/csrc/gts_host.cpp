@@ -31,6 +31,10 @@ struct CompactShape {
   uint64_t nodes;
 };
 
+struct Burst {
+  uint32_t nodes, mem;
+};
+
 struct gts_graph {
   gts::Image img;
   uint64_t bytes;
@@ -38,7 +42,7 @@ struct gts_graph {
   uint64_t max_tile_lines;
   bool all_mem_txn;  // every load / store streams at least one line (transaction-level memory)
   uint32_t full_lanes;  // bit n: at n_subpart = n every compute op holds every subpartition lane
-  uint32_t burst;       // one event readies at least this many nodes of one SM (ready_burst)
+  Burst burst;          // one event readies at least this many nodes of one SM (ready_burst)
   // the kernels with compact template records, those of one shape together,
   // the most nodes first
   std::vector<CompactShape> compact;
@@ -328,28 +332,38 @@ void compact_templates(const gts_graph_host* h, Derived* d) {
   }
 }
 
-// Nodes that become ready together on one SM, at least, in every simulation of
-// the graph that gets so far: the most nodes without in-edges of a CTA (ready
-// at its launch), or successors of one in-edge of a node in its own CTA that
-// are released by one event (a load's or store's ORDER edges at its issue, its
-// others at its completion; all of a compute node's at its issue).
-uint32_t ready_burst(const gts_graph_host* h, const Derived& d) {
-  uint32_t burst = 0;
+// Nodes that one event readies on one SM, at least, in every simulation of the
+// graph that gets so far: the most nodes without in-edges of a CTA (ready at
+// its launch), or successors of one in-edge of a node in its own CTA that are
+// released by one event (a load's or store's ORDER edges at its issue, its
+// others at its completion; all of a compute node's at its issue).  mem: the
+// most loads and stores among them that are ready in the same cycle (a compute
+// node's ORDER edges and its others release in two).
+Burst ready_burst(const gts_graph_host* h, const Derived& d) {
+  Burst burst{0, 0};
   for (uint32_t c = 0; c < h->n_ctas; ++c) {
-    uint32_t roots = 0;
+    Burst roots{0, 0};
     for (uint32_t u = h->cta_node_begin[c]; u < h->cta_node_begin[c + 1]; ++u) {
-      roots += d.indeg[u] == 0;
+      if (d.indeg[u] == 0) {
+        ++roots.nodes;
+        roots.mem += is_memory(h->op_cls[h->node_op[u]]);
+      }
       const uint32_t e0 = h->succ_ptr[u], e1 = h->succ_ptr[u + 1];
-      if (e1 - e0 <= burst) continue;
-      const bool mem = is_memory(h->op_cls[h->node_op[u]]);
-      uint32_t at[2] = {0, 0};
+      if (e1 - e0 <= burst.mem) continue;  // no larger than burst.nodes
+      uint32_t all[2] = {0, 0}, mem[2] = {0, 0};
       for (uint32_t e = e0; e < e1; ++e) {
         const uint32_t v = h->succ[e] & GTS_EDGE_TARGET_MASK;
-        if (d.indeg[v] == 1 && d.node_cta[v] == c) ++at[mem && (h->succ[e] >> GTS_EDGE_KIND_SHIFT) == GTS_EDGE_ORDER];
+        if (d.indeg[v] != 1 || d.node_cta[v] != c) continue;
+        const bool order = (h->succ[e] >> GTS_EDGE_KIND_SHIFT) == GTS_EDGE_ORDER;
+        ++all[order];
+        mem[order] += is_memory(h->op_cls[h->node_op[v]]);
       }
-      burst = std::max(burst, std::max(at[0], at[1]));
+      const uint32_t nodes = is_memory(h->op_cls[h->node_op[u]]) ? std::max(all[0], all[1]) : all[0] + all[1];
+      burst.nodes = std::max(burst.nodes, nodes);
+      burst.mem = std::max(burst.mem, std::max(mem[0], mem[1]));
     }
-    burst = std::max(burst, roots);
+    burst.nodes = std::max(burst.nodes, roots.nodes);
+    burst.mem = std::max(burst.mem, roots.mem);
   }
   return burst;
 }
@@ -834,11 +848,13 @@ bool team_batch(uint32_t B, uint32_t max_nsm) {
   return B <= kTeamMost || max_nsm <= 64u;
 }
 
-// Does a simulation of g surely outgrow the team kernel's ready lists (qp
-// entries per SM in LDS, and its SM's share of those in scratch)?  One more
-// node is out of the list while it is the next to issue.
-bool team_overflows(uint32_t burst, uint32_t qp, uint32_t max_nsm) {
-  return burst > qp + gts::kPoolSpill / ((max_nsm + 63u) / 64u) + 1u;
+// Does a simulation of such bursts surely outgrow the team kernel's ready lists
+// (qp entries per SM in LDS, and its SM's share of those in scratch; one more
+// node is out of the list while it is the next to issue), or its rings (ring
+// arrivals per SM in LDS, kRing in scratch: loads and stores ready in one cycle
+// all issue in that cycle's window, before any of them is served)?
+bool team_overflows(const Burst& burst, uint32_t qp, uint32_t ring, uint32_t max_nsm) {
+  return burst.nodes > qp + gts::kPoolSpill / ((max_nsm + 63u) / 64u) + 1u || burst.mem > ring + gts::kRing;
 }
 
 // LDS one workgroup may have on the current device (0 if it cannot be queried).
@@ -997,13 +1013,14 @@ int launch(const gts_graph* g, const uint32_t* hw_dev, uint32_t B, uint32_t max_
   if (team) {
     gts::Launch T = L;
     const uint32_t lds_team = team_sizes(g, T, wstride);
-    // Such a batch goes straight to the windowed kernel, whose lanes share one
-    // list among their SMs: simulated up to the overflow first, 256
-    // simulations of 4 CTAs with joins of 200 nodes behind 600 single ones
-    // took 10.5 instead of 8.6 ms.  (Lists for them in scratch made the team
-    // kernel the slower one: 1024 simulations of joins of 120 nodes on 44 of
-    // 132 SMs 26.6 ms, on the windowed kernel 15.4.)
-    team = lds_team <= device_lds() && (team_only || !team_overflows(g->burst, T.qp, max_nsm));
+    // A batch that surely overflows goes straight to the windowed kernel, whose
+    // lanes share one list among their SMs: simulated up to the overflow first,
+    // 256 simulations of 4 CTAs with joins of 200 nodes behind 600 single ones
+    // took 10.5 instead of 8.6 ms, and 4096 of 160 loads ready at once on one
+    // SM (the windowed kernel's rings overflow too: 2.4 ms, and 1.2 on the
+    // general kernel) 12.4 instead of 3.7.  (Longer lists would be the faster
+    // way, but a capacity known only at run time costs every case 1-4 %.)
+    team = lds_team <= device_lds() && (team_only || !team_overflows(g->burst, T.qp, T.team_ring, max_nsm));
     if (team) {
       e = gts::launch_team(T, lds_team, st);
       L.retry_only = 1;
@@ -1299,7 +1316,7 @@ int gts_graph_upload(const gts_graph_host* h, void* dev_image, uint64_t dev_byte
   std::sort(g->compact.begin(), g->compact.end(),
             [](const CompactShape& a, const CompactShape& b) { return a.nodes > b.nodes; });
   g->full_lanes = d.full_lanes;
-  g->burst = h->n_nodes ? ready_burst(h, d) : 0u;
+  g->burst = h->n_nodes ? ready_burst(h, d) : Burst{0, 0};
   g->all_mem_txn = d.all_mem_txn;
   const bool txn = !d.txn_line.empty();
   g->img.txn_ptr = txn ? reinterpret_cast<const uint32_t*>(base + L.txn_ptr) : nullptr;

@@ -12,16 +12,20 @@ extern "C" int64_t gts_test_words_after_check(const gts_graph_host* h) {
   return n;
 }
 
-// Nodes that one event readies on one SM, at least.
-extern "C" int64_t gts_test_burst(const gts_graph_host* h) {
+// Nodes, and loads and stores in one cycle, that one event readies on one SM,
+// at least.
+extern "C" int gts_test_burst(const gts_graph_host* h, uint32_t* out) {
   Derived d;
-  if (check_graph(h, &d)) return -1;
-  return h->n_nodes ? (int64_t)ready_burst(h, d) : 0;
+  if (const int rc = check_graph(h, &d)) return rc;
+  const Burst b = ready_burst(h, d);
+  out[0] = b.nodes;
+  out[1] = b.mem;
+  return 0;
 }
 
-// Whether a burst surely outgrows the team kernel's lists.
-extern "C" int gts_test_team_overflows(uint32_t burst, uint32_t qp, uint32_t max_nsm) {
-  return team_overflows(burst, qp, max_nsm);
+// Whether bursts surely outgrow the team kernel's lists or rings.
+extern "C" int gts_test_team_overflows(uint32_t nodes, uint32_t mem, uint32_t qp, uint32_t ring, uint32_t max_nsm) {
+  return team_overflows(Burst{nodes, mem}, qp, ring, max_nsm);
 }
 
 // Per kernel {template nodes, first record, state slots}, then the record

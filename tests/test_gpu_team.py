@@ -215,7 +215,7 @@ def _fan_out(width, kind):
             v = b.node(ALU, 64, 0xF)
             b.edge(u, v)
             u = v
-        mid = [b.node(ALU, 64 + i % 5, 0xF) for i in range(width)]
+        mid = [b.node(GLOAD if kind == "loads" else ALU, 64 + i % 5, 0xF) for i in range(width)]
         join, out = b.node(SYNC, 0, 0xF), b.node(GSTORE, 256, 0xF)
         for m in mid:
             b.edge(u, m, ORDER if kind == "issue" else DATA)
@@ -226,12 +226,13 @@ def _fan_out(width, kind):
     return b.build("fan_out")
 
 
-@pytest.mark.parametrize("kind", ["issue", "completion", "compute"])
+@pytest.mark.parametrize("kind", ["issue", "completion", "compute", "loads"])
 def test_team_bursts(torch_cuda, kind, monkeypatch):
     """What the rule that leaves such graphs to the windowed kernel rests on:
-    a burst past the lists is handed back by every simulation of the batch,
-    one that fits by none."""
-    for width, fits in ((60, True), (300, False)):
+    a burst past the lists (of loads: past the rings, 64 entries beside at most
+    16 in LDS) is handed back by every simulation of the batch, one that fits
+    by none."""
+    for width, fits in ((60, True), (81 if kind == "loads" else 300, False)):
         g = _fan_out(width, kind)
         assert window_eligible(g)
         hws = np.stack([H.preset("H100", n_sm=s, max_cta_per_sm=1) for s in (132, 256, 44, 4)])

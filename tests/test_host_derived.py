@@ -28,7 +28,6 @@ def lib(tmp_path_factory):
                            os.path.join(CSRC, "gts_host_only.cpp"), "-L/opt/rocm/lib", "-lamdhip64", "-o", out])
     L = ctypes.CDLL(out)
     L.gts_test_words_after_check.restype = L.gts_test_compact.restype = ctypes.c_int64
-    L.gts_test_burst.restype = ctypes.c_int64
     L.gts_test_compact.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_uint64]
     return L
 
@@ -185,30 +184,48 @@ def test_queries_build_no_records(lib):
 
 
 def burst(g):
-    """Nodes that one event readies on one SM, at least, written out."""
+    """Nodes, and loads and stores in one cycle, that one event readies on one
+    SM, at least, written out."""
     ptr, succ = np.asarray(g.succ_ptr, np.int64), np.asarray(g.succ, np.int64)
-    tgt, kind = succ & 0x3FFFFFFF, succ >> 30
+    tgt, order = succ & 0x3FFFFFFF, succ >> 30 == ORDER
     src = np.repeat(np.arange(g.n_nodes), np.diff(ptr))
     cta = np.repeat(np.arange(len(g.cta_node_begin) - 1), np.diff(np.asarray(g.cta_node_begin, np.int64)))
     indeg = np.bincount(tgt, minlength=g.n_nodes)
     mem = np.isin(np.asarray(g.op_cls)[np.asarray(g.node_op, np.int64)], (GLOAD, GSTORE))
     alone = (indeg[tgt] == 1) & (cta[src] == cta[tgt])
-    issue = mem[src] & (kind == ORDER)
-    counts = [np.bincount(cta[indeg == 0]), np.bincount(src[alone & issue]), np.bincount(src[alone & ~issue])]
-    return max(int(c.max()) if c.size else 0 for c in counts)
+    event = 2 * src + (order & mem[src])  # a compute node's releases are one event ...
+    cycle = 2 * src + order               # ... in two cycles
+    most = lambda x: int(np.bincount(x).max()) if len(x) else 0  # noqa: E731
+    return (max(most(cta[indeg == 0]), most(event[alone])),
+            max(most(cta[(indeg == 0) & mem]), most(cycle[alone & mem[tgt]])))
 
 
 def test_burst(lib):
     def of(g):
         h, _keep = api._host_struct(g)
-        return lib.gts_test_burst(ctypes.byref(h))
-    for seed in range(100):
-        g = windowed_graph(SplitMix64(seed, 17))
+        out = (ctypes.c_uint32 * 2)()
+        assert lib.gts_test_burst(ctypes.byref(h), out) == 0
+        return tuple(out)
+    for seed in range(200):
+        g = windowed_graph(SplitMix64(seed, 17), nodes=(1, 12 if seed % 2 else 40))
         assert of(g) == burst(g), f"seed {seed}"
-    g = W.splitkv_decode(batch=6, kv_min=64, kv_max=4096, seed=9)
-    assert of(g) == burst(g) > 0
-    assert of(_joins(300)) == 300  # its loads
-    # the pending node beside a full list of qp + 240 / waves entries
+    for seed in range(40):
+        g, _ = single_sink_graph(SplitMix64(seed, 18))
+        assert of(g) == burst(g), f"seed {seed}"
+    assert of(_joins(300)) == (300, 300)  # its loads
+    b = GraphBuilder()  # one event in two cycles: 9 + 3 loads, and 20 other nodes
+    b.kernel(4, 0)
+    b.cta()
+    u = b.node(ALU, 256, 0xF)
+    late = [b.node(GLOAD, 256, 0xF) for _ in range(12)]
+    other = [b.node(ALU, 256, 0xF) for _ in range(20)]
+    out = b.node(GSTORE, 256, 0xF)
+    for i, v in enumerate(late + other):
+        b.edge(u, v, ORDER if i < 5 or i % 2 else DATA)
+        b.edge(v, out)
+    assert of(b.build("two_cycles")) == (32, 9)
+    # the pending node beside a full list of qp + 240 / waves entries; the rings
     for sms, share in ((1, 240), (64, 240), (65, 120), (132, 80), (256, 60)):
-        assert not lib.gts_test_team_overflows(8 + share + 1, 8, sms)
-        assert lib.gts_test_team_overflows(8 + share + 2, 8, sms)
+        assert not lib.gts_test_team_overflows(8 + share + 1, 68, 8, 4, sms)
+        assert lib.gts_test_team_overflows(8 + share + 2, 0, 8, 4, sms)
+        assert lib.gts_test_team_overflows(69, 69, 8, 4, sms)
