@@ -619,10 +619,8 @@ struct TSim {
       e[1] = cyc;
       e[2] = op;
       ++gc;
-    } else {  // handed back: nothing more of this SM needs to run
+    } else {
       bad |= kBadQueue;
-      n = nd = 0;
-      best = ~0ull;
     }
   }
   // d entries leave the front; the LDS part fills up again from scratch
