@@ -261,19 +261,22 @@ class Plan:
         blk = scratch[:b * stride].view(b, stride)[:, stride - 128:].contiguous().view(torch.int64).cpu().numpy()
         return blk[(st[first:first + b] == 0).cpu().numpy()]
 
-    def mostly_on_team(self, api, torch):
-        """Whether the team kernel finishes most simulations: up to eight
-        launches spread over the step, run once more; word 11 of a counter
-        block is the wavefronts of a simulation that the team kernel finished
-        (0 from the windowed kernel)."""
+    def mostly_on_team(self, api, torch, rerun):
+        """Whether the team kernel finishes most simulations, from word 11 of
+        their counter blocks (the wavefronts of a simulation that it finished;
+        0 from the windowed kernel): of the last launch of every stream, or
+        (rerun) of up to eight launches spread over the step, run once more."""
         team = sims = 0
-        for k in sorted(set(np.linspace(0, len(self.launches) - 1, 8).astype(int).tolist())):
+        n, q = len(self.launches), len(self.streams)
+        for k in sorted(set(np.linspace(0, n - 1, 8).astype(int).tolist())) if rerun else range(max(0, n - q), n):
             i, first, b = self.launches[k]
-            dg, hs, (_, mk, st, dgst), _, _ = self.parts[i]
-            api.simulate_hwset_into(dg, hs, first, b, api.OUT_DIGEST, None, mk[first:first + b], st[first:first + b],
-                                    dgst[first:first + b], self.scratches[0], self.streams[0])
-            torch.cuda.synchronize()
-            blk = self.counter_blocks(api, torch, self.scratches[0], i, first, b)
+            scratch = self.scratches[k % q]
+            if rerun:
+                dg, hs, (_, mk, st, dgst), _, _ = self.parts[i]
+                api.simulate_hwset_into(dg, hs, first, b, api.OUT_DIGEST, None, mk[first:first + b],
+                                        st[first:first + b], dgst[first:first + b], scratch, self.streams[k % q])
+                torch.cuda.synchronize()
+            blk = self.counter_blocks(api, torch, scratch, i, first, b)
             team += int((blk[:, 11] > 0).sum())
             sims += len(blk)
         return 2 * team > sims
@@ -471,7 +474,8 @@ def main() -> int:
         print(f"[bench] warmup step {k + 1}/{args.warmup} done", file=sys.stderr, flush=True)
     step_s, launch_s, wall = plan.timed(api, torch, args.steps)
     node_sims, sims, abytes, infeasible = plan.step_totals(per_node)
-    team = name not in ("noc", "txn", "l2lru") and plan.mostly_on_team(api, torch)
+    # profiled runs (no CPU leg) add no launches to the steps asked for
+    team = name not in ("noc", "txn", "l2lru") and plan.mostly_on_team(api, torch, rerun=not args.no_cpu_baseline)
     K = args.steps
     if args.launch_log:
         with open(args.launch_log, "w") as f:
